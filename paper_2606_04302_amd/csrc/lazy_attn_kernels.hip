@@ -680,6 +680,16 @@ __device__ __forceinline__ void attend_tile(const uint16_t* kb, const uint16_t* 
           if (!ok) sa[rb][blk][i] = -INFINITY;
         }
   }
+  if constexpr (NT == 512) {
+    // The eight-wave loop runs at two speeds, set by where this point falls within the 32 bytes of an instruction
+    // fetch: with NoPE keys 3 and 5 dwords past a boundary give 561-564 us on four requests of 33K keys and 256
+    // queries (32 / 8 heads), the other six 590-598 us, and 698 against 756 us with 28 / 4 heads, for identical
+    // instructions; the other key modes are indifferent.  Fixed here, so that a change elsewhere in the kernel (even
+    // of its argument offsets) does not decide it.
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile(".p2align 6\n .rept 5\n s_nop 0\n .endr");
+    __builtin_amdgcn_sched_barrier(0);
+  }
   uint32_t pk[RB][16];  // bf16 pairs of P: block blk, keys 8 (i / 4) + 4 h2 + i % 4 for i = 2 j, 2 j + 1
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {

@@ -50,6 +50,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));  // in a caller's record table
 
 constexpr int kThreads = 256;
 constexpr int kSub = 64;  // keys of one loader sub-tile; tile row 0 of a sub-tile is a multiple of 64 in its chunk
@@ -250,6 +251,18 @@ struct TileIter {
   }
   __device__ void init(const lazy_chunk_t* table, int c0, int c1, int split, int splits, const First& first) {
     recs = as_const(table);
+    if (!locate(table, c0, c1, split, splits, first)) return;
+    const int f = i - c0;
+    if (f < 64) {
+      cur = lane_rec(first.mine, f);
+      if (i + 1 < end) nxt = f + 1 < 64 ? lane_rec(first.mine, f + 1) : load_rec(recs + i + 1);
+    } else {
+      cur = load_rec(recs + i);
+      if (i + 1 < end) nxt = load_rec(recs + i + 1);
+    }
+  }
+  // Number and place of the split's tiles: left, i and j0; false if the split holds none.
+  __device__ bool locate(const lazy_chunk_t* table, int c0, int c1, int split, int splits, const First& first) {
     end = c1;
     const int lane = threadIdx.x & 63;
     const lazy_chunk_t& mine = first.mine;
@@ -273,7 +286,7 @@ struct TileIter {
     left = hi - lo;
     i = c1;
     j0 = 0;
-    if (left <= 0) return;
+    if (left <= 0) return false;
     // Pass 2: the record holding tile lo, the first whose inclusive tile count exceeds lo.
     int acc = 0;
     for (int k0 = c0; k0 < c1; k0 += 64) {
@@ -291,14 +304,7 @@ struct TileIter {
       }
       acc = __builtin_amdgcn_readlane(incl, 63);
     }
-    const int f = i - c0;
-    if (f < 64) {
-      cur = lane_rec(mine, f);
-      if (i + 1 < end) nxt = f + 1 < 64 ? lane_rec(mine, f + 1) : load_rec(recs + i + 1);
-    } else {
-      cur = load_rec(recs + i);
-      if (i + 1 < end) nxt = load_rec(recs + i + 1);
-    }
+    return true;
   }
   // Lane f's record as a wave-uniform value.
   __device__ static Rec lane_rec(const lazy_chunk_t& r, int f) {
@@ -332,19 +338,119 @@ struct TileIter {
     }
     return false;
   }
+};
+
+// The decode's walk: the tiles w, w + 4, ... of a split for wave w.  SORT: the records of a request that has at most
+// kSortMax of them are taken in the order in which their values are stored (sort_records below); a longer table is
+// walked as it is.
+constexpr int kSortMax = 256;  // 64 lanes x 4 indexes of one byte
+template <int TK, bool SORT>
+struct DecodeIter : TileIter<TK> {
+  using Base = TileIter<TK>;
+  using Base::cur, Base::nxt, Base::i, Base::j0, Base::left, Base::end, Base::recs;
+  bool sorted;
+  uint32_t perm;  // byte b of lane l: table index (from the request's first record) of record 64 b + l of the order
+  __device__ Rec rec(int r) const {
+    if (SORT && sorted) r = (uint32_t)__builtin_amdgcn_readlane((int)perm, r & 63) >> (8 * (r >> 6)) & 255;
+    return load_rec(recs + r);
+  }
+  __device__ void init(const lazy_chunk_t* table, int c0, int c1, int split, int splits,
+                       const typename Base::First& first) {
+    sorted = false;
+    Base::init(table, c0, c1, split, splits, first);
+  }
+  // order: the n <= kSortMax table indexes, sorted: their records, both in LDS.  The split's first two records come from
+  // there (a scalar load would be one more round trip before the first tile), the later ones from the table.
+  __device__ void init_sorted(const lazy_chunk_t* table, int c0, int n, int split, int splits, const uint8_t* order,
+                              const lazy_chunk_t* sorted_recs) {
+    sorted = true;
+    recs = as_const(table + c0);
+    const int lane = threadIdx.x & 63;
+    typename Base::First f;
+    f.mine.len = sorted_recs[lane].len;
+    perm = order[lane];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      f.len[u] = sorted_recs[lane + 64 * (u + 1)].len;
+      perm |= (uint32_t)order[lane + 64 * (u + 1)] << (8 * (u + 1));
+    }
+    if (!Base::locate(table, 0, n, split, splits, f)) return;
+    // Lane 0 / 1 hold records i / i + 1 (the last one if there is none).
+    const lazy_chunk_t two = sorted_recs[min(i + (lane & 1), n - 1)];
+    cur = Base::lane_rec(two, 0);
+    if (i + 1 < end) nxt = Base::lane_rec(two, 1);
+  }
+  __device__ void step() {
+    --left;
+    j0 += TK;
+    while (left > 0 && j0 >= cur.len) {
+      ++i;
+      j0 = 0;
+      cur = nxt;
+      if (i + 1 < end) nxt = rec(i + 1);
+    }
+  }
   // Advance by `n` tiles (fewer if the split ends first).
   __device__ void skip(int n) {
     for (int k = 0; k < n && left > 0; ++k) step();
   }
   // seek() for a walker that owns every stride-th tile of the split (the decode waves): invisible tiles are passed
   // over `stride` at a time, so the walker stays on its own residue class of tiles.  Positions need not increase
-  // along the table, so a tile after the query may precede visible ones.
+  // along the walk, so a tile after the query may precede visible ones.
   __device__ bool seek_strided(bool causal, int qmax, int stride) {
     while (left > 0) {
       if (!causal || cur.pos + j0 <= qmax) return true;
       skip(stride);
     }
     return false;
+  }
+};
+
+// Orders a request's n <= kSortMax records by where their values are stored, in LDS; thread t holds record t.  V rather
+// than K: a materialised copy has K offsets of its own but the store's V offsets, and both walks then take the same
+// order.  The key is the 128 KiB unit of the store (24 bits of v_offset / 2^16 elements) with the table index below
+// it, so records of one unit stay in table order: any permutation gives the same attention, the key only has to bring
+// requests that share chunks to them at about the same time.  The rank is the number of smaller keys: uniform 16-byte
+// LDS reads of four keys, eight in flight.
+// Barriers: one between publish and place, one between place and the first use of order / recs.
+static_assert(offsetof(lazy_chunk_t, v_offset) == 8 && offsetof(lazy_chunk_t, len) == 16 && sizeof(lazy_chunk_t) == 32,
+              "a record is two 16-byte words");
+struct RecordSort {
+  lazy_chunk_t recs[kSortMax] __attribute__((aligned(16)));
+  uint32_t key[kSortMax] __attribute__((aligned(16)));
+  uint8_t order[kSortMax];
+  uint32_t unordered[kThreads / 64];  // per wave: some of its records lies before its predecessor in the table
+  __device__ static uint32_t unit_of(u32x2 v_offset) { return (v_offset[0] >> 16 | v_offset[1] << 16) & 0xffffff; }
+  // A record as two 16-byte words (a lazy_chunk_t variable would be indexed memory to the compiler, in LDS or scratch):
+  // lo = k_offset, v_offset; hi = len, pos_offset, k_stride, v_stride.  next: v_offset of the record after it (of the
+  // last record: its own).
+  __device__ void publish(u32x4 lo, u32x2 next, int t, int n) {
+    const uint32_t unit = unit_of(u32x2{lo[2], lo[3]});
+    key[t] = t < n ? unit << 8 | (uint32_t)t : 0xffffffffu;
+    const bool any = __any(t < n && unit_of(next) < unit);
+    if ((t & 63) == 0) unordered[t >> 6] = any;
+  }
+  // After publish's barrier: is there anything to sort?  (A private context from an allocator that only grows is in
+  // order already, and table order is then the sorted order.)
+  __device__ bool needed() const {
+    return uniform((int)(unordered[0] | unordered[1] | unordered[2] | unordered[3])) != 0;
+  }
+  __device__ void place(u32x4 lo, u32x4 hi, int t, int n) {
+    int rank = t;  // entries past n keep their place (the walk never reaches them)
+    if (t < n) {
+      const uint32_t own = key[t];
+      rank = 0;
+      for (int j = 0; j < n; j += 32) {  // entries past n compare greater
+        u32x4 o[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = *reinterpret_cast<const u32x4*>(key + j + 4 * e);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rank += (o[e][0] < own) + (o[e][1] < own) + (o[e][2] < own) + (o[e][3] < own);
+      }
+    }
+    order[rank] = (uint8_t)t;
+    reinterpret_cast<u32x4*>(recs + rank)[0] = lo;
+    reinterpret_cast<u32x4*>(recs + rank)[1] = hi;
   }
 };
 
@@ -1266,7 +1372,7 @@ __device__ __forceinline__ void dec_tile(const DecTile<D>& cur, uint16_t* vw, co
   }
 }
 
-template <int D, int KMI>
+template <int D, int KMI, bool SORT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_kernel(AttnArgs a) {
   __shared__ DecodeSmem<D> sm;
   constexpr int KM = keys_of(KMI);
@@ -1294,7 +1400,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // are zeroed once Q is needed; no load sits behind a per-lane branch, which would make the compiler wait for
   // every load in flight at its first use).  The frequency and per-row tables are built while they are in flight,
   // then the table walk issues this wave's first tile.
+  static_assert(kSortMax == kThreads, "one record per thread");
   const TileIter<kDecWaveKeys>::First first = TileIter<kDecWaveKeys>::first_block(a.chunks, c0, c1);
+  const bool sortable = SORT && c1 > c0 && c1 - c0 <= kSortMax;
+  u32x4 rlo = {}, rhi = {};  // this thread's record (past the end: the last one, ignored below) and the next V offset
+  u32x2 rnext = {};
+  if (sortable) {
+    const u32x4_a8* rec = reinterpret_cast<const u32x4_a8*>(a.chunks + min(c0 + tid, c1 - 1));
+    rlo = rec[0];
+    rhi = rec[1];
+    rnext = *reinterpret_cast<const u32x2*>(&a.chunks[min(c0 + tid + 1, c1 - 1)].v_offset);
+  }
   u32x4 qraw[SP][2];
   {
     const uint16_t* qrow = a.q + ((int64_t)r * a.hq + head) * D;
@@ -1302,10 +1418,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int s = 0; s < SP; ++s) dec_k_pairs<D, IL, false>(qrow, s, kq, qraw[s][0], qraw[s][1]);
   }
   if (!ALIBI && tid < D / 2) sm.freq[tid] = theta_rev(tid, D, a.rope_log2_base, a.inv_freq);
+  // The sort's LDS lies in the V slices, which the tile loop first writes after the last barrier below.
+  static_assert(sizeof(RecordSort) <= sizeof(sm.v), "the record order is formed in the V slices");
+  RecordSort& rs = *reinterpret_cast<RecordSort*>(&sm.v[0][0]);
+  if (sortable) rs.publish(rlo, rnext, tid, c1 - c0);
   __syncthreads();
   // This wave's tiles: every fourth tile of the split, starting at tile `wave`.
-  TileIter<kDecWaveKeys> it;
-  it.init(a.chunks, c0, c1, split, a.splits, first);
+  DecodeIter<kDecWaveKeys, SORT> it;
+  if (sortable && rs.needed()) {
+    rs.place(rlo, rhi, tid, c1 - c0);
+    __syncthreads();
+    it.init_sorted(a.chunks, c0, c1 - c0, split, a.splits, rs.order, rs.recs);
+  } else {
+    it.init(a.chunks, c0, c1, split, a.splits, first);
+  }
   it.skip(wave);
   bool have = it.seek_strided(a.causal, qpos, 4);
   DecTile<D> cur, nxt;
@@ -1866,9 +1992,11 @@ template <int D, int KM>
 hipError_t decode_d(const AttnArgs& a, hipStream_t st) {
   const dim3 grid(a.splits, a.hkv * a.head_groups, a.batch);
   if (a.stream_kv)
-    hipLaunchKernelGGL((decode_kernel<D, KM | kStreamKV>), grid, dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((decode_kernel<D, KM | kStreamKV, false>), grid, dim3(kThreads), 0, st, a);
+  else if (a.sort_records)
+    hipLaunchKernelGGL((decode_kernel<D, KM, true>), grid, dim3(kThreads), 0, st, a);
   else
-    hipLaunchKernelGGL((decode_kernel<D, KM>), grid, dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((decode_kernel<D, KM, false>), grid, dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 

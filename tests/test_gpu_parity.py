@@ -868,6 +868,40 @@ def test_decode_records_out_of_position_order(mode, splits):
         assert torch.equal(out.view(torch.int16), out_m.view(torch.int16))
 
 
+# Batches of at least 1024 keys per split: the decode walks a request's records in the order their values are stored,
+# sorted in the kernel for tables of up to 256 records (one per thread, 64 per wave and index byte).  Request 0 lists
+# its chunks in storage order (nothing to sort), request 1 in reverse, request 2 shuffled with a record after the query
+# in between; the second key length leaves several records in one 128 KiB unit of the sort's key.
+@pytest.mark.parametrize("mode", list(OOO_MODES))
+@pytest.mark.parametrize("n,length", [(2, 700), (63, 33), (64, 20), (65, 20), (255, 6), (256, 5), (257, 5)])
+def test_decode_sorts_records_by_storage(n, length, mode):
+    rng = np.random.default_rng(n)
+    reqs = []
+    for r in range(3):
+        order = list(range(n))
+        if r == 1:
+            order.reverse()
+        elif r == 2:
+            rng.shuffle(order)
+        chunks, pos = [], 0
+        for k, c in enumerate(order):
+            hidden = r == 2 and k == n // 2
+            chunks.append((c, length, 50_000 if hidden else pos))
+            pos += 0 if hidden else length
+        reqs.append(dict(chunks=chunks, q_len=1, q_pos0=pos - 1 - (length // 2 if r == 2 else 0)))
+    w = W.custom(161, 32, 8, 128, 1e4, reqs, kind="decode")
+    assert w.max_kv_len >= 1024
+    ckw = {**OOO_MODES[mode], "num_splits": 1}
+    dw, out, lse = run_and_check(w, f"decode sorted {mode} n={n}", ckw)
+    if mode != "alibi":  # the plain walk over a materialised copy takes the same order
+        (out_m, lse_m), _ = ops.run_materialized(dw, ops.config_of(w, **ckw))
+        torch.cuda.synchronize()
+        ref_o, ref_l = oracle(w, **oracle_kw(ckw))
+        assert_close(out_m, lse_m, ref_o, ref_l, tag=f"plain decode sorted {mode} n={n}")
+        if mode == "nope":
+            assert torch.equal(out.view(torch.int16), out_m.view(torch.int16))
+
+
 # --------------------------------------------------------------------------------------------------------------
 # Positions near LAZY_MAX_POS = 2^24 (the appendix on long-context stability evaluates 128K positions; the ABI
 # allows up to 2^24): angles are reduced in fp64 before the fp32 sine / cosine.

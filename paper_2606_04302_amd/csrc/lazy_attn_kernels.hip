@@ -344,6 +344,7 @@ struct TileIter {
 // kSortMax of them are taken in the order in which their values are stored (sort_records below); a longer table is
 // walked as it is.
 constexpr int kSortMax = 256;  // 64 lanes x 4 indexes of one byte
+constexpr int kSortMinKeys = 128;
 template <int TK, bool SORT>
 struct DecodeIter : TileIter<TK> {
   using Base = TileIter<TK>;
@@ -419,19 +420,21 @@ struct RecordSort {
   lazy_chunk_t recs[kSortMax] __attribute__((aligned(16)));
   uint32_t key[kSortMax] __attribute__((aligned(16)));
   uint8_t order[kSortMax];
-  uint32_t unordered[kThreads / 64];  // per wave: some of its records lies before its predecessor in the table
+  uint32_t unordered[kThreads / 64];  // per wave: one of its records lies after its successor in the table
   __device__ static uint32_t unit_of(u32x2 v_offset) { return (v_offset[0] >> 16 | v_offset[1] << 16) & 0xffffff; }
   // A record as two 16-byte words (a lazy_chunk_t variable would be indexed memory to the compiler, in LDS or scratch):
   // lo = k_offset, v_offset; hi = len, pos_offset, k_stride, v_stride.  next: v_offset of the record after it (of the
   // last record: its own).
-  __device__ void publish(u32x4 lo, u32x2 next, int t, int n) {
+  __device__ void publish(u32x4 lo, uint32_t len, u32x2 next, int t, int n) {
     const uint32_t unit = unit_of(u32x2{lo[2], lo[3]});
     key[t] = t < n ? unit << 8 | (uint32_t)t : 0xffffffffu;
-    const bool any = __any(t < n && unit_of(next) < unit);
+    const bool any = __any(t < n && (int)len >= kSortMinKeys && unit_of(next) < unit);
     if ((t & 63) == 0) unordered[t >> 6] = any;
   }
-  // After publish's barrier: is there anything to sort?  (A private context from an allocator that only grows is in
-  // order already, and table order is then the sorted order.)
+  // After publish's barrier: is there anything to sort?  A private context from an allocator that only grows is in order
+  // already, and table order is then the sorted order.  Records below kSortMinKeys alone are left as they are: the blocks
+  // of a paged store lie in no order that requests share, and every record taken from the order costs a wave a little
+  // (seven requests of up to 460 blocks of 64 keys, head_dim 64: 64.5 us in table order, 68.8 sorted).
   __device__ bool needed() const {
     return uniform((int)(unordered[0] | unordered[1] | unordered[2] | unordered[3])) != 0;
   }
@@ -1432,7 +1435,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // The sort's LDS lies in the V slices, which the tile loop first writes after the last barrier below.
   static_assert(sizeof(RecordSort) <= sizeof(sm.v), "the record order is formed in the V slices");
   RecordSort& rs = *reinterpret_cast<RecordSort*>(&sm.v[0][0]);
-  if (sortable) rs.publish(rlo, rnext, tid, c1 - c0);
+  if (sortable) rs.publish(rlo, rhi[0], rnext, tid, c1 - c0);
   __syncthreads();
   // This wave's tiles: every fourth tile of the split, starting at tile `wave`.
   DecodeIter<kDecWaveKeys, SORT> it;

@@ -4,6 +4,9 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "lazy_attn.h"
 #include "lazy_attn_internal.h"
 
@@ -52,26 +55,77 @@ bool prefill_ragged(int32_t batch, int32_t total_q, int32_t max_q_len) {
   return 4 * (int64_t)total_q < 3 * (int64_t)batch * max_q_len;
 }
 
-// KV splits per request.  Workgroups are (query tile, KV head, request, split); those of a query tile past the end
-// of a shorter request exit at once, so the busy ones number about Hkv * ceil(total_q G / rows per tile) per split.
-// Equal requests: one round of workgroups over the chip.  Ragged query lengths (mean below 3/4 of the maximum)
-// usually come with ragged key lengths, and one round then leaves CUs idle behind the longest requests: aim for
-// about three rounds so that the dispatcher can even out the load.
+// Workgroups per KV split that have rows to work on.  Row tiles of the batch: exact where all requests are as long as
+// the longest, else the rows' tiles and on average half a tile per request for its last one, and at least one each.
+int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, int32_t max_q_len) {
+  const int64_t g = p->num_q_heads / p->num_kv_heads;
+  const int64_t rows_per_tile = (int64_t)lazy::kPrefillRowsPerBlock * prefill_row_blocks(p, max_q_len);
+  const int64_t most = (int64_t)batch * prefill_q_tiles(p, max_q_len);
+  const int64_t row_tiles =
+      (int64_t)total_q >= (int64_t)batch * max_q_len
+          ? most
+          : std::min(most, std::max<int64_t>(batch, ceil_div((int64_t)total_q * g, rows_per_tile) + batch / 2));
+  return row_tiles * p->num_kv_heads;
+}
+
+// KV splits per request.  Workgroups are (query tile, KV head, request, split); those of a query tile past the end of a
+// shorter request exit at once, which leaves `busy` per split.  A CU holds `per_cu` of them: one of 256 rows (LDS), two
+// of 128 rows, three with head_dim 64.  The count is the one with the least estimated time, in key tiles:
+//     sharing * rounds * (tiles per split + prologue) + merge,    rounds = ceil(busy * splits / (256 per_cu)).
+// Until its first tile is done and at its end a workgroup spends about as long as on kPrologueTiles tiles; two or three
+// workgroups on a CU take 1.2 or 1.35 times as long each as one alone; a split batch is merged by a second launch.  A
+// count just past a full round runs the last one nearly empty.  Ragged query lengths (mean below 3/4 of the maximum)
+// usually come with ragged key lengths: the average request is then taken as 0.8 of the longest, which sets the end, and
+// the units of different size fill 0.8 of the slots.  Tiles: max_kv_len / 64, with 15% more for records that end in a
+// partial tile where requests are alike.
+//
+// The constants are a fit over split sweeps of 65 batches (128 and 256 rows, head_dim 64 and 128, busy 2 to 816, 4 to
+// 931 tiles): the chosen count is 4% off each batch's best on average.  One round for equal and three for ragged query
+// lengths, with at least four tiles a split, was 19% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
+// 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; 40 requests of 83
+// tiles, 256 rows, busy 320, one and two splits 342 / 296 us; ragged, busy 176, 81 tiles, fifteen and five splits 153 /
+// 127 us; ragged, busy 272, 422 tiles, four and six 866 / 807 us.  Still missed: records much shorter than a tile,
+// whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us where eleven splits take 147).
+constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 6, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
+constexpr double kSharing[4] = {1, 1, 1.2, 1.35};
+constexpr int64_t kMaxSplits = 64;
+// A handful of workgroups with this few tiles is over before a merge would be: one request of 5 tiles and one KV head
+// 14.4 us unsplit, 18.4 with five splits.
+constexpr int64_t kUnsplitTiles = 6;
+
 int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, int32_t max_q_len,
                    int32_t max_kv_len) {
   if (p->num_splits > 0) return p->num_splits;
-  const int64_t g = p->num_q_heads / p->num_kv_heads;
-  const int64_t rows_per_tile = (int64_t)lazy::kPrefillRowsPerBlock * prefill_row_blocks(p, max_q_len);
-  const int64_t busy = (int64_t)p->num_kv_heads * ceil_div((int64_t)total_q * g, rows_per_tile);
-  const int64_t tiles = ceil_div(max_kv_len, lazy::kPrefillTileKeys);
-  // 256-row workgroups occupy a whole CU (LDS), 128-row ones leave room for two per CU.
-  const int64_t slots = prefill_row_blocks(p, max_q_len) == 2 ? kNumCUs : 2 * kNumCUs;
-  const int64_t target = prefill_ragged(batch, total_q, max_q_len) ? 3 * slots : slots;
-  int64_t s = busy > 0 ? ceil_div(target, busy) : 1;
-  const int64_t cap = tiles / 4 > 1 ? tiles / 4 : 1;  // keep at least ~4 key tiles per split
-  if (s > cap) s = cap;
-  if (s > 64) s = 64;
-  return s < 1 ? 1 : (int)s;
+  const int per_cu = prefill_row_blocks(p, max_q_len) == 2 ? 1 : p->head_dim == 64 ? 3 : 2;
+  const int64_t tiles = std::max<int64_t>(1, ceil_div(max_kv_len, lazy::kPrefillTileKeys));
+  const bool ragged = prefill_ragged(batch, total_q, max_q_len);
+  const double busy = (double)prefill_busy(p, batch, total_q, max_q_len);
+  const double slots = (double)(kNumCUs * per_cu) * (ragged ? 0.8 : 1.0);
+  if (tiles <= kUnsplitTiles && busy < kNumCUs / 64) return 1;
+  int64_t best = 1;
+  double least = 0;
+  for (int64_t s = 1; s <= std::min(tiles, kMaxSplits); ++s) {
+    const double groups = busy * (double)s, rounds = std::ceil(groups / slots);
+    const double sharing = kSharing[(int)std::min((double)per_cu, std::ceil(groups / kNumCUs))];
+    const double merge = s > 1 ? kMergeTiles + kMergeTilesPerSplit * (double)s : 0;
+    double cost;
+    if (ragged) {
+      const double per = (double)(tiles + 1) / (double)s;
+      cost = rounds * (0.8 * per + kRaggedPrologueTiles) + 0.5 * (per + kRaggedPrologueTiles);
+    } else {
+      cost = rounds * ((1.15 * (double)tiles + 1) / (double)s + kPrologueTiles);
+    }
+    cost = sharing * cost + merge;
+    if (s == 1 || cost < least) {
+      best = s;
+      least = cost;
+    }
+  }
+  // A ragged batch is not left in one piece while two of four tiles are to be had (busy 240, 9 tiles: 127 us with one
+  // split, 121 with two; busy 239, 13 tiles: 83 and 90 us).
+  if (ragged && best == 1 && tiles >= 8) best = 2;
+  // The grid's z axis holds batch x splits.
+  return (int)std::max<int64_t>(1, std::min<int64_t>(best, batch > 0 ? 65535 / batch : best));
 }
 
 int decode_head_groups(const lazy_attn_params_t* p) {
@@ -151,6 +205,9 @@ int run_prefill(bool rotate_k, const lazy_attn_params_t* p, const void* q, const
   a.splits = splits;
   a.q_tiles = q_tiles;
   a.row_blocks = prefill_row_blocks(p, max_q_len);
+  // Three workgroups a CU (head_dim 64) where the launch has more than two for each; below that the third wave's tighter
+  // register allotment (a few spills) only costs (39 requests of up to 5 tiles, 320 workgroups: 23.3 against 21.5 us).
+  a.crowded = prefill_busy(p, batch, total_q, max_q_len) * splits > 2 * kNumCUs;
   // Ragged batches spread their (request, split) units over the XCDs; alike requests keep whole requests per XCD.
   a.xcd_interleave = prefill_ragged(batch, total_q, max_q_len);
   a.head_groups = 1;

@@ -899,9 +899,13 @@ __device__ __forceinline__ void attend_tile(const uint16_t* kb, const uint16_t* 
   __builtin_amdgcn_s_setprio(0);
 }
 
-template <int D, int KMI, int NW, int NBUF, int RB>
+// WPE: waves per SIMD that the registers are allotted for.  head_dim 128 has room for two; head_dim 64 fits three (168
+// registers, 33 KB of LDS a workgroup, so three workgroups a CU): a tile's products are half as long there against the
+// same softmax, and a third workgroup fills the waits (eight requests of ~5K keys and 101 queries, 32 / 8 heads, three
+// splits: 138 us with two, 107 with three; four would spill: 750 us; two with double-buffered tiles 121 us).
+template <int D, int KMI, int NW, int NBUF, int RB, int WPE>
 __global__ __launch_bounds__(NW * 64)
-__attribute__((amdgpu_waves_per_eu(RB == 1 ? 2 : 1, RB == 1 ? 2 : 1))) void prefill_kernel(AttnArgs a) {
+__attribute__((amdgpu_waves_per_eu(WPE, WPE))) void prefill_kernel(AttnArgs a) {
   __shared__ PrefillSmem<D, NBUF> sm;
   constexpr int KM = keys_of(KMI);
   constexpr bool ALIBI = KM == kKeysAlibi;
@@ -1993,12 +1997,19 @@ hipError_t prefill_d(const AttnArgs& a, hipStream_t st) {
   const dim3 grid(a.q_tiles, a.hkv, a.batch * a.splits);
   if constexpr (D == 128) {
     if (a.row_blocks == 2) {
-      hipLaunchKernelGGL((prefill_kernel<D, KM, LAZY_PREFILL_BIG_WAVES, 2, 8 / LAZY_PREFILL_BIG_WAVES>), grid,
-                         dim3(64 * LAZY_PREFILL_BIG_WAVES), 0, st, a);
+      hipLaunchKernelGGL((prefill_kernel<D, KM, LAZY_PREFILL_BIG_WAVES, 2, 8 / LAZY_PREFILL_BIG_WAVES,
+                                         LAZY_PREFILL_BIG_WAVES / 4>),
+                         grid, dim3(64 * LAZY_PREFILL_BIG_WAVES), 0, st, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((prefill_kernel<D, KM, 4, 1, 1>), grid, dim3(kThreads), 0, st, a);
+  if constexpr (D == 64) {
+    if (a.crowded) {
+      hipLaunchKernelGGL((prefill_kernel<D, KM, 4, 1, 1, 3>), grid, dim3(kThreads), 0, st, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((prefill_kernel<D, KM, 4, 1, 1, 2>), grid, dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -944,6 +944,20 @@ def test_eight_wave_prefill_short_splits(mode):
         run_and_check(w, f"eight-wave prefill {mode} splits={splits}", {**ckw, "num_splits": splits})
 
 
+# head_dim 64 prefill launches of more than 512 busy workgroups take the kernel with registers for three waves per SIMD:
+# ragged tails of rows and keys, a request without a full tile, splits of one to three tiles.
+@pytest.mark.parametrize("mode", ["nope", "local", "interleaved", "alibi"])
+def test_prefill_d64_three_waves(mode):
+    reqs = [dict(chunks=[(70 + 9 * i, 0), (200, 70 + 9 * i), (130 - i, 400)], q_len=130 - i, q_pos0=400)
+            for i in range(11)]
+    reqs.append(dict(chunks=[(3, 0)], q_len=3, q_pos0=0))
+    w = W.custom(191, 16, 8, 64, 1e4, reqs)
+    row_tiles = -(-w.total_q * (w.num_q_heads // w.num_kv_heads) // 128) + w.batch // 2  # the launch's estimate
+    for splits in (3, 4):
+        assert row_tiles * w.num_kv_heads * splits > 512
+        run_and_check(w, f"prefill d64 three waves {mode} splits={splits}", {**OOO_MODES[mode], "num_splits": splits})
+
+
 # --------------------------------------------------------------------------------------------------------------
 # Chunk tables in storage order (lazy_chunk_table_storage_order): the same records, each request's sorted by
 # k_offset.  Positions decide the attention, so the results match the oracle of the position-ordered table, and the

@@ -773,6 +773,17 @@ __device__ __forceinline__ void attend_tile(const uint16_t* kb, const uint16_t* 
     }
   }
   __builtin_amdgcn_s_setprio(0);
+  if constexpr (NT == 512) {
+    // The eight-wave loop runs at two speeds, set by where the code from here to the probabilities falls within the 32
+    // bytes of an instruction fetch: with NoPE keys 0 and 2 dwords past a boundary give 561-562 us on four requests of
+    // 33K keys and 256 queries (32 / 8 heads), the other six 594-598 us, and 698 against 756 us with 28 / 4 heads, for
+    // identical instructions; the other key modes are indifferent.  Fixed here, so that a change elsewhere in the
+    // kernel (even of its argument offsets) does not decide it.  Two dwords past 32 bytes run the fewest s_nops of the
+    // good positions tried (3 or 5 past a boundary after the mask: 0.5% slower).
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile(".p2align 5\n s_nop 0\n s_nop 0");
+    __builtin_amdgcn_sched_barrier(0);
+  }
   if (ALIBI) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
@@ -796,16 +807,6 @@ __device__ __forceinline__ void attend_tile(const uint16_t* kb, const uint16_t* 
           const bool ok = kk < nvalid && (!causal || b0 + kk <= qpos[rb]);
           if (!ok) sa[rb][blk][i] = -INFINITY;
         }
-  }
-  if constexpr (NT == 512) {
-    // The eight-wave loop runs at two speeds, set by where this point falls within the 32 bytes of an instruction
-    // fetch: with NoPE keys 3 and 5 dwords past a boundary give 561-564 us on four requests of 33K keys and 256
-    // queries (32 / 8 heads), the other six 590-598 us, and 698 against 756 us with 28 / 4 heads, for identical
-    // instructions; the other key modes are indifferent.  Fixed here, so that a change elsewhere in the kernel (even
-    // of its argument offsets) does not decide it.
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile(".p2align 6\n .rept 5\n s_nop 0\n .endr");
-    __builtin_amdgcn_sched_barrier(0);
   }
   uint32_t pk[RB][16];  // bf16 pairs of P: block blk, keys 8 (i / 4) + 4 h2 + i % 4 for i = 2 j, 2 j + 1
 #pragma unroll

@@ -74,19 +74,21 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 //     sharing * rounds * (tiles per split + prologue) + merge,    rounds = ceil(busy * splits / (256 per_cu)).
 // Until its first tile is done and at its end a workgroup spends about as long as on kPrologueTiles tiles; two or three
 // workgroups on a CU take 1.2 or 1.35 times as long each as one alone; a split batch is merged by a second launch.  A
-// count just past a full round runs the last one nearly empty.  Ragged query lengths (mean below 3/4 of the maximum)
-// usually come with ragged key lengths: the average request is then taken as 0.8 of the longest, which sets the end, and
-// the units of different size fill 0.8 of the slots.  Tiles: max_kv_len / 64, with 15% more for records that end in a
-// partial tile where requests are alike.
+// count just past a full round runs the last one nearly empty.  Tiles: max_kv_len / 64, with 15% more for records that
+// end in a partial tile.  Ragged query lengths (mean below 3/4 of the maximum) usually come with ragged key lengths: the
+// average request is then taken as 0.8 of the longest, which sets the end; the units of different size fill 0.8 of the
+// slots, and the dispatcher evens out most of the last round (a quarter of it is counted as lost); 75% more tiles, since
+// splits too few are dearer there than splits too many.
 //
-// The constants are a fit over split sweeps of 65 batches (128 and 256 rows, head_dim 64 and 128, busy 2 to 816, 4 to
+// The constants are a fit over split sweeps of 66 batches (128 and 256 rows, head_dim 64 and 128, busy 2 to 816, 4 to
 // 931 tiles): the chosen count is 4% off each batch's best on average.  One round for equal and three for ragged query
 // lengths, with at least four tiles a split, was 19% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
 // 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; 40 requests of 83
 // tiles, 256 rows, busy 320, one and two splits 342 / 296 us; ragged, busy 176, 81 tiles, fifteen and five splits 153 /
 // 127 us; ragged, busy 272, 422 tiles, four and six 866 / 807 us.  Still missed: records much shorter than a tile,
-// whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us where eleven splits take 147).
-constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 6, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
+// whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us where eleven splits take 147; blocks
+// of 32 keys, busy 176: 335 us where six take 313).
+constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 4, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
 constexpr double kSharing[4] = {1, 1, 1.2, 1.35};
 constexpr int64_t kMaxSplits = 64;
 // A handful of workgroups with this few tiles is over before a merge would be: one request of 5 tiles and one KV head
@@ -105,15 +107,16 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   int64_t best = 1;
   double least = 0;
   for (int64_t s = 1; s <= std::min(tiles, kMaxSplits); ++s) {
-    const double groups = busy * (double)s, rounds = std::ceil(groups / slots);
+    const double groups = busy * (double)s, n = groups / slots;
     const double sharing = kSharing[(int)std::min((double)per_cu, std::ceil(groups / kNumCUs))];
     const double merge = s > 1 ? kMergeTiles + kMergeTilesPerSplit * (double)s : 0;
     double cost;
     if (ragged) {
-      const double per = (double)(tiles + 1) / (double)s;
-      cost = rounds * (0.8 * per + kRaggedPrologueTiles) + 0.5 * (per + kRaggedPrologueTiles);
+      const double per = (1.75 * (double)tiles + 1) / (double)s;
+      cost = (0.25 * std::ceil(n) + 0.75 * std::max(1.0, n)) * (0.8 * per + kRaggedPrologueTiles) +
+             0.3 * (per + kRaggedPrologueTiles);
     } else {
-      cost = rounds * ((1.15 * (double)tiles + 1) / (double)s + kPrologueTiles);
+      cost = std::ceil(n) * ((1.15 * (double)tiles + 1) / (double)s + kPrologueTiles);
     }
     cost = sharing * cost + merge;
     if (s == 1 || cost < least) {
@@ -147,12 +150,13 @@ int decode_splits(const lazy_attn_params_t* p, int32_t batch, int32_t max_kv_len
 
 // Requests that share chunks list them in orders of their own, so each reads them at another time and the caches hold
 // little for the next.  The decode therefore walks a request's records in the order their values are stored (outputs
-// change only in the order of the sums): four requests over one pool of 128 exemplars, 33K keys each, 84.4 -> 63.4 us a
-// step; 64 requests with sixteen of 256 chunks of 1024 keys, 581 -> 527 us.  Sorting takes a workgroup 0.5-2 us, so it
-// is left out where that shows: one request, or under 1024 keys per split (10K keys in 16 splits: 20.8 -> 21.3 us; two
+// change only in the order of the sums): four requests over one pool of 128 exemplars, 33K keys each, 84.1 -> 63.2 us a
+// step; 64 requests with sixteen of 256 chunks of 1024 keys, 583 -> 526 us.  Sorting takes a workgroup 0.5-2 us and
+// finding that there is nothing to sort about 1 us, so it is left out where that shows: one request, or under 1536 keys
+// per split (10K keys in 16 splits: 20.8 -> 21.3 us; 52 requests of 6.4K keys in 5 splits, in order: 36.8 -> 38.1 us; two
 // requests of 2.6K keys in 13 splits: 16.9 -> 17.3 us), and with the hint that the caches will not be asked again.
 bool decode_sorted(const lazy_attn_params_t* p, int32_t batch, int splits, int32_t max_kv_len) {
-  return batch > 1 && p->cache_hint != LAZY_CACHE_STREAM && max_kv_len / splits >= 1024;
+  return batch > 1 && p->cache_hint != LAZY_CACHE_STREAM && max_kv_len / splits >= 1536;
 }
 
 // Split-KV workspace: bf16 normalised partial outputs [splits][rows][d], then fp32 partial lse [splits][rows]

@@ -868,12 +868,12 @@ def test_decode_records_out_of_position_order(mode, splits):
         assert torch.equal(out.view(torch.int16), out_m.view(torch.int16))
 
 
-# Batches of at least 1024 keys per split: the decode walks a request's records in the order their values are stored,
+# Batches of at least 1536 keys per split: the decode walks a request's records in the order their values are stored,
 # sorted in the kernel for tables of up to 256 records (one per thread, 64 per wave and index byte).  Request 0 lists
 # its chunks in storage order (nothing to sort), request 1 in reverse, request 2 shuffled with a record after the query
 # in between; two of the shorter records share one 128 KiB unit of the sort's key.  Records under 128 keys are not sorted.
 @pytest.mark.parametrize("mode", list(OOO_MODES))
-@pytest.mark.parametrize("n,length", [(2, 700), (9, 127), (63, 130), (64, 128), (65, 128), (255, 128), (256, 129),
+@pytest.mark.parametrize("n,length", [(2, 900), (13, 127), (63, 130), (64, 128), (65, 128), (255, 128), (256, 129),
                                       (257, 128)])
 def test_decode_sorts_records_by_storage(n, length, mode):
     rng = np.random.default_rng(n)
@@ -891,7 +891,7 @@ def test_decode_sorts_records_by_storage(n, length, mode):
             pos += 0 if hidden else length
         reqs.append(dict(chunks=chunks, q_len=1, q_pos0=pos - 1 - (length // 2 if r == 2 else 0)))
     w = W.custom(161, 8, 2, 128, 1e4, reqs, kind="decode")
-    assert w.max_kv_len >= 1024
+    assert w.max_kv_len >= 1536
     ckw = {**OOO_MODES[mode], "num_splits": 1}
     dw, out, lse = run_and_check(w, f"decode sorted {mode} n={n}", ckw)
     if mode != "alibi":  # the plain walk over a materialised copy takes the same order

@@ -276,6 +276,13 @@ def test_combine_entry_point_matches_oracle_merge(s, rows, d):
     assert_close(out, lse, ref_o, ref_l, tag="combine")
 
 
+# From 8192 rows the merge of 5 to 16 splits uses fewer lanes a row: both sides of the row count and of 8 / 16 splits.
+@pytest.mark.parametrize("s,rows,d", [(5, 8192, 128), (8, 8209, 64), (8, 8191, 128), (9, 8200, 64), (16, 8193, 128),
+                                      (17, 8192, 64)])
+def test_combine_many_rows(s, rows, d):
+    test_combine_entry_point_matches_oracle_merge(s, rows, d)
+
+
 def test_edge_cases_empty_request_no_visible_key_len1_chunks_nan_slack():
     reqs = [
         dict(chunks=[(5, 100)], q_len=3, q_pos0=2),                        # keys after every query: none visible

@@ -85,10 +85,10 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 // lengths, with at least four tiles a split, was 19% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
 // 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; 40 requests of 83
 // tiles, 256 rows, busy 320, one and two splits 342 / 296 us; ragged, busy 176, 81 tiles, fifteen and five splits 153 /
-// 127 us; ragged, busy 272, 422 tiles, four and six 866 / 807 us.  Still missed: records much shorter than a tile,
+// 127 us; ragged, busy 272, 422 tiles, four and six 866 / 792 us.  Still missed: records much shorter than a tile,
 // whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us where eleven splits take 147; blocks
 // of 32 keys, busy 176: 335 us where six take 313), and which requests are the long ones (two ragged batches of busy 272
-// and 264 and 422 and 437 tiles: four and six splits 866 and 807 us on one, 882 and 924 on the other).
+// and 264 and 422 and 437 tiles: four and six splits 866 and 792 us on one, 870 and 901 on the other).
 constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 4, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
 constexpr double kSharing[4] = {1, 1, 1.2, 1.35};
 constexpr int64_t kMaxSplits = 64;

@@ -83,8 +83,7 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 // The constants are a fit over split sweeps of 66 batches (128 and 256 rows, head_dim 64 and 128, busy 2 to 816, 4 to
 // 931 tiles): the chosen count is 4% off each batch's best on average.  One round for equal and three for ragged query
 // lengths, with at least four tiles a split, was 19% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
-// 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; 40 requests of 83
-// tiles, 256 rows, busy 320, one and two splits 342 / 296 us; ragged, busy 176, 81 tiles, fifteen and five splits 153 /
+// 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; ragged, busy 176, 81 tiles, fifteen and five splits 153 /
 // 127 us; ragged, busy 272, 422 tiles, four and six 866 / 792 us.  Still missed: records much shorter than a tile,
 // whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us where eleven splits take 147; blocks
 // of 32 keys, busy 176: 335 us where six take 313), and which requests are the long ones (two ragged batches of busy 272
@@ -92,9 +91,11 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 4, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
 constexpr double kSharing[4] = {1, 1, 1.2, 1.35};
 constexpr int64_t kMaxSplits = 64;
-// A handful of workgroups with this few tiles is over before a merge would be: one request of 5 tiles and one KV head
-// 14.4 us unsplit, 18.4 with five splits.
-constexpr int64_t kUnsplitTiles = 6;
+// A split batch's outputs pass through bf16 partials, an unsplit one's are rounded once (one request of 8 tiles, seven
+// splits: error against 64 bits 0.0035 instead of 0.0032).  A batch with fewer than kSplitTiles tiles, or whose rows alone
+// fill the chip (three times over if ragged), is therefore never split, also where it would be faster so (40 requests of
+// 83 tiles, busy 320: 342 us, two splits 296).
+constexpr int64_t kSplitTiles = 8;
 
 int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, int32_t max_q_len,
                    int32_t max_kv_len) {
@@ -104,7 +105,10 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   const bool ragged = prefill_ragged(batch, total_q, max_q_len);
   const double busy = (double)prefill_busy(p, batch, total_q, max_q_len);
   const double slots = (double)(kNumCUs * per_cu) * (ragged ? 0.8 : 1.0);
-  if (tiles <= kUnsplitTiles && busy < kNumCUs / 64) return 1;
+  const int64_t rows = (int64_t)total_q * (p->num_q_heads / p->num_kv_heads);
+  const int64_t per_tile = (int64_t)lazy::kPrefillRowsPerBlock * prefill_row_blocks(p, max_q_len);
+  const int64_t full = (int64_t)kNumCUs * (per_cu == 1 ? 1 : 2) * (ragged ? 3 : 1);
+  if (tiles < kSplitTiles || p->num_kv_heads * ceil_div(rows, per_tile) >= full) return 1;
   int64_t best = 1;
   double least = 0;
   for (int64_t s = 1; s <= std::min(tiles, kMaxSplits); ++s) {
@@ -125,9 +129,9 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
       least = cost;
     }
   }
-  // A ragged batch is not left in one piece while two of four tiles are to be had (busy 240, 9 tiles: 127 us with one
-  // split, 121 with two; busy 239, 13 tiles: 83 and 90 us).
-  if (ragged && best == 1 && tiles >= 8) best = 2;
+  // A ragged batch is not left in one piece otherwise (busy 240, 9 tiles: 127 us with one split, 121 with two; busy 239,
+  // 13 tiles: 83 and 90 us).
+  if (ragged && best == 1) best = 2;
   // The grid's z axis holds batch x splits.
   return (int)std::max<int64_t>(1, std::min<int64_t>(best, batch > 0 ? 65535 / batch : best));
 }

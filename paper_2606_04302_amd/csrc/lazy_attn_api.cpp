@@ -136,6 +136,18 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   return (int)std::max<int64_t>(1, std::min<int64_t>(best, batch > 0 ? 65535 / batch : best));
 }
 
+// Which workgroups of a ragged prefill stay together on an XCD.  One unit per KV head evens out the XCDs, one per request
+// and split reads its table once: the former from kUnitHeadsTiles tiles a split.  Four requests of 96-143K keys, two to
+// eight splits: 14.3 / 11.8 / 14.4 / 11.1 / 12.2 / 11.0 / 9.8 ms by request, 10.8 / 11.1 / 10.4 / 10.2 / 10.3 / 10.2 /
+// 10.1 by head (eight splits put a part of each request on every XCD); 16 requests of up to 27.6K keys in six splits (72
+// tiles) 809 -> 798 us; 11 of 9.9K in five (31 tiles) 335 -> 338; 16 of 4.7K in seven (10 tiles) 124.1 -> 126.3 us.
+constexpr int64_t kUnitHeadsTiles = 48;
+
+int prefill_units(int32_t batch, int32_t total_q, int32_t max_q_len, int32_t max_kv_len, int splits) {
+  if (!prefill_ragged(batch, total_q, max_q_len)) return lazy::kUnitNone;
+  return max_kv_len / lazy::kPrefillTileKeys >= kUnitHeadsTiles * splits ? lazy::kUnitHeads : lazy::kUnitRequests;
+}
+
 int decode_head_groups(const lazy_attn_params_t* p) {
   const int g = p->num_q_heads / p->num_kv_heads;
   return (g + lazy::kDecodeHeadsPerGroup - 1) / lazy::kDecodeHeadsPerGroup;
@@ -217,8 +229,8 @@ int run_prefill(bool rotate_k, const lazy_attn_params_t* p, const void* q, const
   // Three workgroups a CU (head_dim 64) where the launch has more than two for each; below that the third wave's tighter
   // register allotment (a few spills) only costs (39 requests of up to 5 tiles, 320 workgroups: 23.3 against 21.5 us).
   a.crowded = prefill_busy(p, batch, total_q, max_q_len) * splits > 2 * kNumCUs;
-  // Ragged batches spread their (request, split) units over the XCDs; alike requests keep whole requests per XCD.
-  a.xcd_interleave = prefill_ragged(batch, total_q, max_q_len);
+  // Ragged batches spread units over the XCDs; alike requests keep whole requests per XCD.
+  a.xcd_interleave = prefill_units(batch, total_q, max_q_len, max_kv_len, splits);
   a.head_groups = 1;
   a.rope_log2_base = p->inv_freq || p->rope_style == LAZY_ALIBI ? 0.0 : log2((double)p->rope_base);
   a.scale_log2 = scale_log2(p);

@@ -543,9 +543,11 @@ __device__ __forceinline__ const uint16_t* v_ptr(const uint16_t* pool, const Rec
 // maps from L to the logical workgroup:
 //  - contiguous (uniform batches): XCD k takes the k-th eighth of the logical ids, i.e. whole requests with all of
 //    their heads and splits, which measured fastest when requests are alike;
-//  - interleaved (ragged batches): the nx row tiles and ny heads of one (request, split) unit z stay on one XCD,
-//    and unit z runs on XCD z % 8 (its XCD's m-th workgroup is tile m % (nx ny) of unit z = L % 8 + 8 (m / (nx ny))),
-//    so requests of different lengths are spread evenly over the XCDs instead of piling onto some of them.
+//  - interleaved (ragged batches): the workgroups of one unit stay on one XCD and unit u runs on XCD u % 8 (its XCD's
+//    m-th workgroup is number m % inner of unit L % 8 + 8 (m / inner)).  A unit is a (request, split) with its row tiles
+//    and heads, whose table is then read through one L2, or, with long splits, a (request, split, KV head): heads share
+//    no keys, and spread over the XCDs they give each the same work whatever the requests' lengths, where two or four
+//    splits a request leave the longest requests to a few XCDs (lazy::kUnitHeads).
 // Both fall back to the identity where the counts do not divide by 8.
 // Both maps are evaluated and one is selected, with no branch: the kernel's first loads then issue together.
 __device__ __forceinline__ int xcd_remap(int id, int n, int inner, int units, bool interleave) {
@@ -920,8 +922,10 @@ __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void prefill_kernel(AttnArgs a) {
   // the split count, and right after it the index-array pointers (otherwise loaded one round trip later).
   asm volatile("" ::"s"(a.q_start), "s"(a.chunk_start), "s"(a.splits), "s"(a.xcd_interleave), "s"(nx), "s"(ny),
                "s"(gridDim.z));
-  const int lid = uniform(xcd_remap(blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z), nx * ny * gridDim.z, nx * ny,
-                                    gridDim.z, a.xcd_interleave != 0));
+  const int lid = uniform(xcd_remap(blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z), nx * ny * gridDim.z,
+                                    a.xcd_interleave == kUnitHeads ? nx : nx * ny,
+                                    a.xcd_interleave == kUnitHeads ? ny * gridDim.z : gridDim.z,
+                                    a.xcd_interleave != kUnitNone));
   const int qtile = lid % nx;
   const int g = (lid / nx) % ny;
   const int zz = lid / (nx * ny);
@@ -2117,8 +2121,8 @@ hipError_t combine_splits(const uint16_t* part_o, const float* part_lse, int spl
                           int hq, uint16_t* out, float* lse, hipStream_t st) {
   if (splits <= 4) return combine_d<D, 1, 4>(part_o, part_lse, splits, rows, slot_start, hq, out, lse, st);
   // Many rows fill the chip with few lanes each, and every lane group beyond the splits' need only loads its own padding
-  // (U x CG = 32 slots for six splits): 61K rows of six splits 33.9 -> 17.6 us, 15K rows of seven 10.8 -> 6.7; few rows keep the wide form, whose lanes
-  // are then the only parallelism.
+  // (U x CG = 32 slots for six splits): 61K rows of six splits 33.9 -> 17.6 us, 15K rows of seven 10.8 -> 6.7; few rows
+  // keep the wide form, whose lanes are then the only parallelism.
   if (rows >= kCombineManyRows && splits <= 8)
     return combine_d<D, 1, 8>(part_o, part_lse, splits, rows, slot_start, hq, out, lse, st);
   if (rows >= kCombineManyRows && splits <= 16)

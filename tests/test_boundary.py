@@ -209,7 +209,7 @@ def test_workspace_size_matches_split_formula(ops):
 
 def test_prefill_xcd_map_choice(ops):
     """The interleaved XCD map applies to ragged batches (mean query length under 3/4 of the maximum) whose
-    batch x splits is a multiple of 8; the prefill parity case varlen_g7_b8 is built to take it."""
+    batch x splits x KV heads is a multiple of 8; the prefill parity case varlen_g7_b8 is built to take it."""
     w = W.varlen_rag(seed=30, batch=8, hq=28, hkv=4, d=128, pool_chunks=10, len_lo=40, len_hi=300, k_lo=2, k_hi=4,
                      q_lo=10, q_hi=90)
     cfg = ops.config_of(w)

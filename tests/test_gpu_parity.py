@@ -965,6 +965,20 @@ def test_prefill_d64_three_waves(mode):
         run_and_check(w, f"prefill d64 three waves {mode} splits={splits}", {**OOO_MODES[mode], "num_splits": splits})
 
 
+# Ragged prefill batches place (request, split) units on XCDs, or (request, split, KV head) units from 48 tiles a split,
+# where their number is a multiple of 8, and run in grid order otherwise: all of these, with one and several row tiles.
+@pytest.mark.parametrize("tiles", [4, 47, 48])
+@pytest.mark.parametrize("hq,hkv,splits", [(16, 8, 1), (28, 4, 2), (28, 4, 3), (4, 1, 2), (8, 2, 4)])
+@pytest.mark.parametrize("d,q_max", [(128, 90), (64, 40)])
+def test_ragged_prefill_unit_placement(hq, hkv, splits, d, q_max, tiles):
+    lens = [q_max, 1, 17]
+    keys = [64 * tiles * splits, 70, 900]
+    reqs = [dict(chunks=[(k - n, 0), (n, k - n)], q_len=n, q_pos0=k - n) for k, n in zip(keys, lens)]
+    w = W.custom(211, hq, hkv, d, 1e4, reqs)
+    assert 4 * w.total_q < 3 * w.batch * w.max_q_len and w.max_kv_len == max(keys)
+    run_and_check(w, f"ragged units {hq}/{hkv} d={d} q={q_max} splits={splits}", dict(num_splits=splits))
+
+
 # --------------------------------------------------------------------------------------------------------------
 # Chunk tables in storage order (lazy_chunk_table_storage_order): the same records, each request's sorted by
 # k_offset.  Positions decide the attention, so the results match the oracle of the position-ordered table, and the

@@ -55,6 +55,13 @@ bool prefill_ragged(int32_t batch, int32_t total_q, int32_t max_q_len) {
   return 4 * (int64_t)total_q < 3 * (int64_t)batch * max_q_len;
 }
 
+// Split-KV workspace: bf16 normalised partial outputs [splits][rows][d], then fp32 partial lse [splits][rows]
+// (16-byte aligned because d is a multiple of 8).
+size_t split_workspace(int splits, int64_t rows, int d) {
+  if (splits <= 1) return 0;
+  return (size_t)splits * (size_t)rows * ((size_t)d * sizeof(uint16_t) + sizeof(float));
+}
+
 // Workgroups per KV split that have rows to work on.  Row tiles of the batch: exact where all requests are as long as
 // the longest, else the rows' tiles and on average half a tile per request for its last one, and at least one each.
 int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, int32_t max_q_len) {
@@ -83,11 +90,12 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 // The constants are a fit over split sweeps of 66 batches (128 and 256 rows, head_dim 64 and 128, busy 2 to 816, 4 to
 // 931 tiles): the chosen count is 4% off each batch's best on average.  One round for equal and three for ragged query
 // lengths, with at least four tiles a split, was 19% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
-// 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; ragged, busy 176, 81 tiles, fifteen and five splits 153 /
-// 127 us; ragged, busy 272, 422 tiles, four and six 866 / 792 us.  Still missed: records much shorter than a tile,
-// whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us where eleven splits take 147; blocks
-// of 32 keys, busy 176: 335 us where six take 313), and which requests are the long ones (two ragged batches of busy 272
-// and 264 and 422 and 437 tiles: four and six splits 866 and 792 us on one, 870 and 901 on the other).
+// 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; ragged, busy 176,
+// 81 tiles, fifteen and five splits 153 / 127 us; ragged, busy 272, 422 tiles, four and six 866 / 792 us.  Still missed:
+// records much shorter than a tile, whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us
+// where eleven splits take 147; blocks of 32 keys, busy 176: 335 us where six take 313), and which requests are the long
+// ones (two ragged batches of busy 272 and 264 and 422 and 437 tiles: four and six splits 866 and 792 us on one, 870 and
+// 901 on the other).
 constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 4, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
 constexpr double kSharing[4] = {1, 1, 1.2, 1.35};
 constexpr int64_t kMaxSplits = 64;
@@ -96,6 +104,11 @@ constexpr int64_t kMaxSplits = 64;
 // fill the chip (three times over if ragged), is therefore never split, also where it would be faster so (40 requests of
 // 83 tiles, busy 320: 342 us, two splits 296).
 constexpr int64_t kSplitTiles = 8;
+// Past the fitted lengths every further split of a ragged batch looks a little cheaper, and the partials would reach
+// 1 GB; they are held to this (the rows of a batch that may be split leave room for four splits and more).  Four requests
+// of 96-143K keys, six splits under it and sixteen without: 10.3 and 10.1 ms; 32 requests of 94-147K keys, seven and
+// eleven: 14.0 and 14.0 ms.
+constexpr int64_t kSplitScratch = (int64_t)256 << 20;
 
 int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, int32_t max_q_len,
                    int32_t max_kv_len) {
@@ -109,9 +122,11 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   const int64_t per_tile = (int64_t)lazy::kPrefillRowsPerBlock * prefill_row_blocks(p, max_q_len);
   const int64_t full = (int64_t)kNumCUs * (per_cu == 1 ? 1 : 2) * (ragged ? 3 : 1);
   if (tiles < kSplitTiles || p->num_kv_heads * ceil_div(rows, per_tile) >= full) return 1;
+  const int64_t per_split = (int64_t)split_workspace(2, (int64_t)total_q * p->num_q_heads, p->head_dim) / 2;
+  const int64_t most = std::min({tiles, kMaxSplits, kSplitScratch / std::max<int64_t>(1, per_split)});
   int64_t best = 1;
   double least = 0;
-  for (int64_t s = 1; s <= std::min(tiles, kMaxSplits); ++s) {
+  for (int64_t s = 1; s <= most; ++s) {
     const double groups = busy * (double)s, n = groups / slots;
     const double sharing = kSharing[(int)std::min((double)per_cu, std::ceil(groups / kNumCUs))];
     const double merge = s > 1 ? kMergeTiles + kMergeTilesPerSplit * (double)s : 0;
@@ -174,13 +189,6 @@ int decode_splits(const lazy_attn_params_t* p, int32_t batch, int32_t max_kv_len
 // requests of 2.6K keys in 13 splits: 16.9 -> 17.3 us), and with the hint that the caches will not be asked again.
 bool decode_sorted(const lazy_attn_params_t* p, int32_t batch, int splits, int32_t max_kv_len) {
   return batch > 1 && p->cache_hint != LAZY_CACHE_STREAM && max_kv_len / splits >= 1536;
-}
-
-// Split-KV workspace: bf16 normalised partial outputs [splits][rows][d], then fp32 partial lse [splits][rows]
-// (16-byte aligned because d is a multiple of 8).
-size_t split_workspace(int splits, int64_t rows, int d) {
-  if (splits <= 1) return 0;
-  return (size_t)splits * (size_t)rows * ((size_t)d * sizeof(uint16_t) + sizeof(float));
 }
 
 int status(hipError_t e) { return e == hipSuccess ? LAZY_OK : LAZY_EHIP; }

@@ -226,9 +226,11 @@ def test_prefill_xcd_map_choice(ops):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("batch,q_mean,q_max,kv", [(1, 1, 1, 0), (1, 16, 16, 272), (3, 20, 64, 500), (8, 64, 64, 5312),
                                                    (16, 100, 256, 27000), (400, 3, 8, 700), (40000, 1, 2, 900),
-                                                   (65535, 1, 1, 64), (65535, 1, 2, 4096), (1, 4, 4, 1 << 20)])
+                                                   (65535, 1, 1, 64), (65535, 1, 2, 4096), (1, 4, 4, 1 << 20),
+                                                   (8, 600, 1000, 1 << 17), (2, 4000, 8000, 1 << 20),
+                                                   (7, 200, 200, 1 << 20)])
 def test_prefill_split_count_stays_in_its_range(ops, d, batch, q_mean, q_max, kv):
-    """1 to 64 splits, never more than the keys have tiles, batch x splits within the grid's 65535."""
+    """1 to 64 splits, never more than the keys have tiles, batch x splits within the grid's 65535, 256 MiB of scratch."""
     cfg = ops.Config(32, 8, d, 5e5)
     total_q = batch * q_mean
     n = ops.prefill_workspace_size(cfg, batch, total_q, q_max, kv)
@@ -236,6 +238,7 @@ def test_prefill_split_count_stays_in_its_range(ops, d, batch, q_mean, q_max, kv
     assert n % per_split == 0
     splits = max(1, n // per_split)
     assert 1 <= splits <= min(64, max(1, -(-kv // 64))) and batch * splits <= 65535
+    assert n <= 256 << 20
 
 
 def test_strerror_and_version(ops):

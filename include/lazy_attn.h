@@ -320,8 +320,8 @@ LAZY_API int lazy_shared_decode_plan(const lazy_attn_params_t* params, const laz
  * a table in either order gives the same result up to the order of the floating-point sums.  Why a caller would want
  * it: requests whose tables list the chunks they share in the same order read those chunks together, through one L2
  * or the last-level cache, instead of each from memory.  The decode entry points already walk tables of up to 256
- * records in storage order by themselves (batches of several requests with at least 1536 keys per split, default
- * cache hint); a table given in storage order spares them the sort (about 2 us with 129 records) and brings the
+ * records in storage order by themselves (batches of several requests with at least 1536 keys per split, whatever
+ * the cache hint); a table given in storage order spares them the sort (about 2 us with 129 records) and brings the
  * effect to longer tables.  The chunk-major shared decode's planner wants tables in
  * position order instead (it chains the blocks a request reads back to back).  Returns LAZY_EINVAL for a bad
  * chunk_start (not starting at 0, decreasing) or missing arrays.

@@ -186,9 +186,9 @@ int decode_splits(const lazy_attn_params_t* p, int32_t batch, int32_t max_kv_len
 // step; 64 requests with sixteen of 256 chunks of 1024 keys, 583 -> 526 us.  Sorting takes a workgroup 0.5-2 us and
 // finding that there is nothing to sort about 1 us, so it is left out where that shows: one request, or under 1536 keys
 // per split (10K keys in 16 splits: 20.8 -> 21.3 us; 52 requests of 6.4K keys in 5 splits, in order: 36.8 -> 38.1 us; two
-// requests of 2.6K keys in 13 splits: 16.9 -> 17.3 us), and with the hint that the caches will not be asked again.
-bool decode_sorted(const lazy_attn_params_t* p, int32_t batch, int splits, int32_t max_kv_len) {
-  return batch > 1 && p->cache_hint != LAZY_CACHE_STREAM && max_kv_len / splits >= 1536;
+// requests of 2.6K keys in 13 splits: 16.9 -> 17.3 us).  The cache hint has no say: it must not change a result.
+bool decode_sorted(int32_t batch, int splits, int32_t max_kv_len) {
+  return batch > 1 && max_kv_len / splits >= 1536;
 }
 
 int status(hipError_t e) { return e == hipSuccess ? LAZY_OK : LAZY_EHIP; }
@@ -296,7 +296,7 @@ int run_decode(bool rotate_k, const lazy_attn_params_t* p, const void* q, const 
   a.alibi = p->rope_style == LAZY_ALIBI;
   a.q_prerot = p->q_prerotated && p->rope_style != LAZY_ALIBI;
   a.stream_kv = p->cache_hint == LAZY_CACHE_STREAM;
-  a.sort_records = decode_sorted(p, batch, splits, max_kv_len);
+  a.sort_records = decode_sorted(batch, splits, max_kv_len);
   return status(lazy::launch_decode(a, p->head_dim, rotate_k, static_cast<hipStream_t>(stream)));
 }
 

@@ -2022,7 +2022,9 @@ hipError_t prefill_d(const AttnArgs& a, hipStream_t st) {
 template <int D, int KM>
 hipError_t decode_d(const AttnArgs& a, hipStream_t st) {
   const dim3 grid(a.splits, a.hkv * a.head_groups, a.batch);
-  if (a.stream_kv)
+  if (a.stream_kv && a.sort_records)
+    hipLaunchKernelGGL((decode_kernel<D, KM | kStreamKV, true>), grid, dim3(kThreads), 0, st, a);
+  else if (a.stream_kv)
     hipLaunchKernelGGL((decode_kernel<D, KM | kStreamKV, false>), grid, dim3(kThreads), 0, st, a);
   else if (a.sort_records)
     hipLaunchKernelGGL((decode_kernel<D, KM, true>), grid, dim3(kThreads), 0, st, a);

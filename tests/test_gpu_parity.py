@@ -910,6 +910,40 @@ def test_decode_sorts_records_by_storage(n, length, mode):
             assert torch.equal(out.view(torch.int16), out_m.view(torch.int16))
 
 
+# The hint changes how K and V are read and not the order of a walk: tables that are sorted with the one are sorted with
+# the other (one request in storage order, one reversed, one shuffled).
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("mode", [*OOO_MODES, "plain", "noalloc"])
+def test_stream_cache_hint_sorted_decode_is_bitwise_the_default(mode, splits):
+    rng = np.random.default_rng(5)
+    lens = [int(n) for n in rng.integers(1, 400, 40)]
+    reqs = []
+    for order in (np.arange(40), np.arange(40)[::-1], rng.permutation(40)):
+        pos = np.concatenate([[0], np.cumsum([lens[c] for c in order])])
+        reqs.append(dict(chunks=[(int(c), lens[c], int(p)) for c, p in zip(order, pos)], q_len=1, q_pos0=int(pos[-1])))
+    w = W.custom(162, 8, 2, 128, 1e4, reqs, kind="decode")
+    assert w.max_kv_len // splits >= 1536
+    dw = ops.upload(w)
+    res = []
+    for hint in (ops.CACHE_DEFAULT, ops.CACHE_STREAM):
+        cfg = ops.config_of(w, num_splits=splits, cache_hint=hint, **OOO_MODES.get(mode, {}))
+        if mode == "plain":
+            res.append(ops.run_materialized(dw, cfg)[0])
+        elif mode == "noalloc":
+            out = torch.empty_like(dw.q)
+            lse = torch.empty((w.total_q, w.num_q_heads), dtype=torch.float32, device="cuda")
+            ops.decode_noalloc(cfg, dw.q, dw.q_pos0, dw.pool, dw.pool, dw.chunks, dw.chunk_start, w.max_kv_len, out, lse)
+            res.append((out, lse))
+        else:
+            res.append(ops.run_lazy(dw, cfg))
+    torch.cuda.synchronize()
+    (o0, l0), (o1, l1) = res
+    assert torch.equal(o0.view(torch.int16), o1.view(torch.int16)) and torch.equal(l0, l1)
+    if mode != "plain":
+        ref_o, ref_l = oracle(w, **oracle_kw(OOO_MODES.get(mode)))
+        assert_close(o1, l1, ref_o, ref_l, tag=f"stream hint sorted {mode} splits={splits}")
+
+
 # --------------------------------------------------------------------------------------------------------------
 # Positions near LAZY_MAX_POS = 2^24 (the appendix on long-context stability evaluates 128K positions; the ABI
 # allows up to 2^24): angles are reduced in fp64 before the fp32 sine / cosine.

@@ -158,7 +158,12 @@ typedef struct lazy_attn_params {
  *   out          [total_q][Hq][D] bf16, fully overwritten
  *   lse          [total_q][Hq] fp32 natural-log sum-exp of the scaled scores, or NULL
  *   workspace    device scratch of at least lazy_attn_prefill_workspace_size(...) bytes (may be NULL if 0)
+ * The size belongs to the arguments it was asked for.  It is the split count times the rows, and the count is chosen
+ * for each batch: a smaller batch, also a part of a larger one, or a shorter context can need more (0 bytes where the
+ * rows alone fill the chip, several splits where they do not).  Ask for each call, or keep one buffer of
+ * LAZY_PREFILL_WORKSPACE_MAX bytes: with num_splits = 0 no call needs more.
  */
+#define LAZY_PREFILL_WORKSPACE_MAX (256 << 20)
 LAZY_API int lazy_attn_prefill(const lazy_attn_params_t* params, const void* q, const int32_t* q_start,
                       const int32_t* q_pos0, const void* k_pool, const void* v_pool, const lazy_chunk_t* chunks,
                       const int32_t* chunk_start, int32_t batch, int32_t total_q, int32_t max_q_len,

@@ -105,10 +105,9 @@ constexpr int64_t kMaxSplits = 64;
 // 83 tiles, busy 320: 342 us, two splits 296).
 constexpr int64_t kSplitTiles = 8;
 // Past the fitted lengths every further split of a ragged batch looks a little cheaper, and the partials would reach
-// 1 GB; they are held to this (the rows of a batch that may be split leave room for four splits and more).  Four requests
-// of 96-143K keys, six splits under it and sixteen without: 10.3 and 10.1 ms; 32 requests of 94-147K keys, seven and
-// eleven: 14.0 and 14.0 ms.
-constexpr int64_t kSplitScratch = (int64_t)256 << 20;
+// 1 GB; they are held to LAZY_PREFILL_WORKSPACE_MAX.  The rows of a batch that may be split (above) are less than 768
+// tiles of 256 or 1536 of 128, 51 MB a split at most, so at least five splits fit.  Four requests of 96-143K keys, six
+// splits under it and sixteen without: 10.3 and 10.1 ms; 32 requests of 94-147K keys, seven and eleven: 14.0 and 14.0 ms.
 
 int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, int32_t max_q_len,
                    int32_t max_kv_len) {
@@ -123,7 +122,8 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   const int64_t full = (int64_t)kNumCUs * (per_cu == 1 ? 1 : 2) * (ragged ? 3 : 1);
   if (tiles < kSplitTiles || p->num_kv_heads * ceil_div(rows, per_tile) >= full) return 1;
   const int64_t per_split = (int64_t)split_workspace(2, (int64_t)total_q * p->num_q_heads, p->head_dim) / 2;
-  const int64_t most = std::min({tiles, kMaxSplits, kSplitScratch / std::max<int64_t>(1, per_split)});
+  const int64_t most =
+      std::min({tiles, kMaxSplits, (int64_t)LAZY_PREFILL_WORKSPACE_MAX / std::max<int64_t>(1, per_split)});
   int64_t best = 1;
   double least = 0;
   for (int64_t s = 1; s <= most; ++s) {

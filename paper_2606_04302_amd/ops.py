@@ -183,6 +183,9 @@ def _chunks(t):
           "chunks must be a contiguous device uint8 tensor of 32-byte lazy_chunk_t records")
 
 
+PREFILL_WORKSPACE_MAX = 256 << 20  # LAZY_PREFILL_WORKSPACE_MAX
+
+
 def prefill_workspace_size(cfg: Config, batch: int, total_q: int, max_q_len: int, max_kv_len: int) -> int:
     p = cfg.c()
     return int(lib().lazy_attn_prefill_workspace_size(ctypes.byref(p), batch, total_q, max_q_len, max_kv_len))

@@ -241,6 +241,25 @@ def test_prefill_split_count_stays_in_its_range(ops, d, batch, q_mean, q_max, kv
     assert n <= 256 << 20
 
 
+def test_prefill_workspace_never_exceeds_its_stated_maximum(ops):
+    """One buffer of PREFILL_WORKSPACE_MAX bytes serves every batch and every part of it, which may need more than the
+    batch itself: shapes over the range of rows, heads and lengths, those that split most at the bound among them."""
+    rng = np.random.default_rng(3)
+    header = open(os.path.join(ROOT, "include", "lazy_attn.h")).read()
+    assert "#define LAZY_PREFILL_WORKSPACE_MAX (256 << 20)" in header and ops.PREFILL_WORKSPACE_MAX == 256 << 20
+    most, grows = 0, 0
+    for _ in range(4000):
+        hq, hkv = [(32, 8), (28, 4), (8, 8), (16, 1), (128, 4), (1, 1)][rng.integers(6)]
+        cfg = ops.Config(hq, hkv, int(rng.choice([64, 128])), 5e5)
+        q = rng.integers(1, int(2 ** rng.uniform(1, 13)) + 1, int(2 ** rng.uniform(0, 7)))
+        kv = int(2 ** rng.uniform(6, 24))
+        size = [ops.prefill_workspace_size(cfg, len(part), int(part.sum()), int(part.max()), kv)
+                for part in (q, q[:rng.integers(1, len(q) + 1)])]
+        most, grows = max(most, *size), grows + (size[1] > size[0])
+    assert 128 << 20 < most <= ops.PREFILL_WORKSPACE_MAX
+    assert grows > 0  # why a buffer is not sized by the largest batch
+
+
 def test_strerror_and_version(ops):
     assert ops.strerror(0) == "success"
     assert "workspace" in ops.strerror(-3)

@@ -875,15 +875,34 @@ def test_decode_records_out_of_position_order(mode, splits):
         assert torch.equal(out.view(torch.int16), out_m.view(torch.int16))
 
 
+def _one_by_one(dw, cfg, tables):
+    """Each request decoded in a call of its own over the table given for it.  Calls of one request are never sorted, so
+    these are the bits of a walk in table order."""
+    w, res = dw.w, []
+    for r, t in enumerate(tables):
+        lse = torch.empty((1, w.num_q_heads), dtype=torch.float32, device="cuda")
+        chunks = torch.from_numpy(np.ascontiguousarray(t).view(np.uint8).copy()).cuda()
+        start = torch.tensor([0, len(t)], dtype=torch.int32, device="cuda")
+        res.append(ops.decode(cfg, dw.q[r:r + 1], dw.q_pos0[r:r + 1], dw.pool, dw.pool, chunks, start, w.max_kv_len,
+                              lse=lse))
+    torch.cuda.synchronize()
+    return torch.cat([o for o, _ in res]), torch.cat([l for _, l in res])
+
+
 # Batches of at least 1536 keys per split: the decode walks a request's records in the order their values are stored,
-# sorted in the kernel for tables of up to 256 records (one per thread, 64 per wave and index byte).  Request 0 lists
-# its chunks in storage order (nothing to sort), request 1 in reverse, request 2 shuffled with a record after the query
-# in between; two of the shorter records share one 128 KiB unit of the sort's key.  Records under 128 keys are not sorted.
+# sorted in the kernel for tables of up to 256 records (one per thread, 64 per wave and index byte) by the 128 KiB unit
+# that holds them, table order within a unit.  Request 0 lists its chunks in storage order (nothing to sort), request 1
+# in reverse, request 2 shuffled with a record after the query in between.  From 63 records on their lengths are mixed,
+# from one key to twice `length`, several of them in one unit.  Tables of 257 records, or of records under 128 keys alone, are
+# walked as they are.  One and several splits (the later ones start within the sorted table), both head dimensions, one
+# and two head groups.
 @pytest.mark.parametrize("mode", list(OOO_MODES))
-@pytest.mark.parametrize("n,length", [(2, 900), (13, 127), (63, 130), (64, 128), (65, 128), (255, 128), (256, 129),
-                                      (257, 128)])
-def test_decode_sorts_records_by_storage(n, length, mode):
+@pytest.mark.parametrize("n,length,hq,d,splits", [(2, 900, 8, 128, 1), (13, 127, 8, 128, 1), (63, 130, 8, 64, 2),
+                                                  (64, 128, 8, 128, 1), (65, 128, 12, 64, 3), (255, 128, 40, 128, 2),
+                                                  (256, 129, 8, 64, 5), (256, 129, 8, 128, 1), (257, 128, 8, 128, 2)])
+def test_decode_sorts_records_by_storage(n, length, hq, d, splits, mode):
     rng = np.random.default_rng(n)
+    lens = [int(x) for x in rng.integers(1, 2 * length, n)] if n >= 63 else [length] * n
     reqs = []
     for r in range(3):
         order = list(range(n))
@@ -894,13 +913,26 @@ def test_decode_sorts_records_by_storage(n, length, mode):
         chunks, pos = [], 0
         for k, c in enumerate(order):
             hidden = r == 2 and k == n // 2
-            chunks.append((c, length, 50_000 if hidden else pos))
-            pos += 0 if hidden else length
+            chunks.append((c, lens[c], 50_000 if hidden else pos))
+            pos += 0 if hidden else lens[c]
         reqs.append(dict(chunks=chunks, q_len=1, q_pos0=pos - 1 - (length // 2 if r == 2 else 0)))
-    w = W.custom(161, 8, 2, 128, 1e4, reqs, kind="decode")
-    assert w.max_kv_len >= 1536
-    ckw = {**OOO_MODES[mode], "num_splits": 1}
+    w = W.custom(161, hq, 2, d, 1e4, reqs, kind="decode")
+    assert w.max_kv_len // splits >= 1536
+    ckw = {**OOO_MODES[mode], "num_splits": splits}
     dw, out, lse = run_and_check(w, f"decode sorted {mode} n={n}", ckw)
+    tables = [w.chunks[w.chunk_start[r]:w.chunk_start[r + 1]] for r in range(3)]
+    o_t, l_t = _one_by_one(dw, ops.config_of(w, **ckw), tables)
+    in_order = n > 256 or max(lens) < 128
+    if in_order:
+        o_s, l_s = o_t, l_t
+    else:
+        units = [t["v_offset"] >> 16 for t in tables]
+        tables = [t[np.argsort(u, kind="stable")] for t, u in zip(tables, units)]
+        o_s, l_s = _one_by_one(dw, ops.config_of(w, **ckw), tables)
+        if n >= 63:  # the order shows in the bits, so that a walk left unsorted would not pass
+            assert any(len(np.unique(u)) < n for u in units)
+            assert not torch.equal(o_s[1], o_t[1]) and not torch.equal(o_s[2], o_t[2])
+    assert torch.equal(out.view(torch.int16), o_s.view(torch.int16)) and torch.equal(lse, l_s)
     if mode != "alibi":  # the plain walk over a materialised copy takes the same order
         (out_m, lse_m), _ = ops.run_materialized(dw, ops.config_of(w, **ckw))
         torch.cuda.synchronize()

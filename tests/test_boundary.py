@@ -232,7 +232,7 @@ def test_prefill_xcd_map_choice(ops):
                                                    (8, 600, 1000, 1 << 17), (2, 4000, 8000, 1 << 20),
                                                    (7, 200, 200, 1 << 20)])
 def test_prefill_split_count_stays_in_its_range(ops, d, batch, q_mean, q_max, kv):
-    """1 to 64 splits, never more than the keys have tiles, batch x splits within the grid's 65535, 256 MiB of scratch."""
+    """1 to 64 splits, never more than the keys have tiles, 256 MiB of scratch (the grid's limit: the next test)."""
     cfg = ops.Config(32, 8, d, 5e5)
     total_q = batch * q_mean
     n = ops.prefill_workspace_size(cfg, batch, total_q, q_max, kv)
@@ -241,6 +241,16 @@ def test_prefill_split_count_stays_in_its_range(ops, d, batch, q_mean, q_max, kv
     splits = max(1, n // per_split)
     assert 1 <= splits <= min(64, max(1, -(-kv // 64))) and batch * splits <= 65535
     assert n <= 256 << 20
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("batch,splits", [(20000, 2), (32767, 2), (32768, 1), (40000, 1), (65535, 1)])
+def test_prefill_split_count_is_held_to_the_grid(ops, d, batch, splits):
+    """Ragged batches of one head and fourteen key tiles want two splits; past 32767 requests two would exceed the 65535
+    of the grid's z axis (batch x splits), and the call is not refused but left unsplit."""
+    cfg = ops.Config(1, 1, d, 1e4)
+    n = ops.prefill_workspace_size(cfg, batch, batch, 2, 900)
+    assert n == (2 * batch * (2 * d + 4) if splits == 2 else 0)
 
 
 def test_prefill_workspace_never_exceeds_its_stated_maximum(ops):

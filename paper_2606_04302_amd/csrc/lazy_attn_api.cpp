@@ -91,11 +91,13 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 // 931 tiles): the chosen count is 4% off each batch's best on average.  One round for equal and three for ragged query
 // lengths, with at least four tiles a split, was 19% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
 // 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; ragged, busy 176,
-// 81 tiles, fifteen and five splits 153 / 127 us; ragged, busy 272, 422 tiles, four and six 866 / 792 us.  Still missed:
-// records much shorter than a tile, whose number the lengths do not tell (records of 6 to 51 keys, busy 144: 166 us
-// where eleven splits take 147; blocks of 32 keys, busy 176: 335 us where six take 313), and which requests are the long
-// ones (two ragged batches of busy 272 and 264 and 422 and 437 tiles: four and six splits 866 and 792 us on one, 870 and
-// 901 on the other).
+// 81 tiles, fifteen and five splits 153 / 127 us.  Longer batches than the fitted ones, eight of equal requests with
+// 1030 to 2340 tiles: the chosen count within 2% of the best of one to seventeen splits, on one 9% off (two splits 1.92
+// ms, seventeen 1.76).  Close estimates are followed too: nine requests of 2340 tiles at head_dim 64 get seventeen
+// splits on 1.7% less than for two, and take 3.01 ms instead of 3.44.  Four and six splits on four ragged batches of
+// busy 240 to 272 and 377 to 437 tiles, with units of one KV head (prefill_units): 790 / 798, 898 / 878, 800 / 779 and
+// 749 / 723 us.  Still missed: records much shorter than a tile, whose number the lengths do not tell (records of 6 to
+// 51 keys, busy 144: 166 us where eleven splits take 147; blocks of 32 keys, busy 176: 335 us where six take 313).
 constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 4, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
 constexpr double kSharing[4] = {1, 1, 1.2, 1.35};
 constexpr int64_t kMaxSplits = 64;
@@ -183,9 +185,11 @@ int decode_splits(const lazy_attn_params_t* p, int32_t batch, int32_t max_kv_len
 // Requests that share chunks list them in orders of their own, so each reads them at another time and the caches hold
 // little for the next.  The decode therefore walks a request's records in the order their values are stored (outputs
 // change only in the order of the sums): four requests over one pool of 128 exemplars, 33K keys each, 84.1 -> 63.2 us a
-// step; 64 requests with sixteen of 256 chunks of 1024 keys, 583 -> 526 us.  Sorting takes a workgroup 0.5-2 us and
-// finding that there is nothing to sort about 1 us, so it is left out where that shows: one request, or under 1536 keys
-// per split (10K keys in 16 splits: 20.8 -> 21.3 us; 52 requests of 6.4K keys in 5 splits, in order: 36.8 -> 38.1 us; two
+// step; 64 requests with sixteen of 256 chunks of 1024 keys, 583 -> 526 us; with the stream hint 88.6 -> 80.7 and 622
+// -> 608. Sorting takes a workgroup 0.5-2 us and finding that there is nothing to sort 0.2-0.8 us (private contexts in
+// order: four requests of 33K keys 101.0 -> 101.8 us, with the stream hint 92.8 -> 93.1, at head_dim 64 55.5 -> 56.2
+// and 48.7 -> 49.4; 64 of 4K 184.5 -> 184.7), so it is left out where that shows: one request, or under 1536 keys per
+// split (10K keys in 16 splits: 20.8 -> 21.3 us; 52 requests of 6.4K keys in 5 splits, in order: 36.8 -> 38.1 us; two
 // requests of 2.6K keys in 13 splits: 16.9 -> 17.3 us).  The cache hint has no say: it must not change a result.
 bool decode_sorted(int32_t batch, int splits, int32_t max_kv_len) {
   return batch > 1 && max_kv_len / splits >= 1536;

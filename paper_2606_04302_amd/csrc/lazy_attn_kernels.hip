@@ -431,10 +431,11 @@ struct RecordSort {
     const bool any = __any(t < n && (int)len >= kSortMinKeys && unit_of(next) < unit);
     if ((t & 63) == 0) unordered[t >> 6] = any;
   }
-  // After publish's barrier: is there anything to sort?  A private context from an allocator that only grows is in order
-  // already, and table order is then the sorted order.  Records below kSortMinKeys alone are left as they are: the blocks
-  // of a paged store lie in no order that requests share, and every record taken from the order costs a wave a little
-  // (seven requests of up to 460 blocks of 64 keys, head_dim 64: 64.5 us in table order, 68.8 sorted).
+  // After publish's barrier: is there anything to sort?  A private context from an allocator that only grows is in
+  // order already, and table order is then the sorted order.  Only neighbours are compared, and only where the first of
+  // the two is not short: long records in disorder with short ones between them stay as they are.  So do short records
+  // alone: the blocks of a paged store lie in no order that requests share, and every record taken from the order costs
+  // a wave a little (seven requests of up to 460 blocks of 64 keys, head_dim 64: 64.5 us in table order, 68.8 sorted).
   __device__ bool needed() const {
     return uniform((int)(unordered[0] | unordered[1] | unordered[2] | unordered[3])) != 0;
   }
@@ -902,10 +903,12 @@ __device__ __forceinline__ void attend_tile(const uint16_t* kb, const uint16_t* 
   __builtin_amdgcn_s_setprio(0);
 }
 
-// WPE: waves per SIMD that the registers are allotted for.  head_dim 128 has room for two; head_dim 64 fits three (168
+// WPE: waves per SIMD that the registers are allotted for.  head_dim 128 has room for two; head_dim 64 takes three (168
 // registers, 33 KB of LDS a workgroup, so three workgroups a CU): a tile's products are half as long there against the
 // same softmax, and a third workgroup fills the waits (eight requests of ~5K keys and 101 queries, 32 / 8 heads, three
-// splits: 138 us with two, 107 with three; four would spill: 750 us; two with double-buffered tiles 121 us).
+// splits: 138 us with two, 107 with three; two with double-buffered tiles 121 us).  Three already spill 8 to 13
+// registers (36 to 56 bytes of scratch a lane), values that do not change in the loop: stored before it, read back three
+// to seven times a tile.  With four the loop lives in scratch (750 us).
 template <int D, int KMI, int NW, int NBUF, int RB, int WPE>
 __global__ __launch_bounds__(NW * 64)
 __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void prefill_kernel(AttnArgs a) {

@@ -76,8 +76,11 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 }
 
 // KV splits per request.  Workgroups are (query tile, KV head, request, split); those of a query tile past the end of a
-// shorter request exit at once, which leaves `busy` per split.  A CU holds `per_cu` of them: one of 256 rows (LDS), two
-// of 128 rows, three with head_dim 64.  The count is the one with the least estimated time, in key tiles:
+// shorter request exit at once, which leaves `busy` per split in a ragged batch.  Where the lengths are nearly equal
+// all that are launched count, with rows or without, since a launch of more than a round's workgroups begins a second
+// round on some XCDs (two requests of 102 queries and 27K keys, 40 / 8 heads, 32 workgroups of which 24 have rows:
+// eight splits 155 us, nine 262).  A CU holds `per_cu` of them: one of 256 rows (LDS), two of 128 rows, three with
+// head_dim 64.  The count is the one with the least estimated time, in key tiles:
 //     sharing * rounds * (tiles per split + prologue) + merge,    rounds = ceil(busy * splits / (256 per_cu)).
 // Until its first tile is done and at its end a workgroup spends about as long as on kPrologueTiles tiles; two or three
 // workgroups on a CU take 1.2 or 1.35 times as long each as one alone; a split batch is merged by a second launch.  A
@@ -117,7 +120,8 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   const int per_cu = prefill_row_blocks(p, max_q_len) == 2 ? 1 : p->head_dim == 64 ? 3 : 2;
   const int64_t tiles = std::max<int64_t>(1, ceil_div(max_kv_len, lazy::kPrefillTileKeys));
   const bool ragged = prefill_ragged(batch, total_q, max_q_len);
-  const double busy = (double)prefill_busy(p, batch, total_q, max_q_len);
+  const double launched = (double)batch * prefill_q_tiles(p, max_q_len) * p->num_kv_heads;
+  const double busy = ragged ? (double)prefill_busy(p, batch, total_q, max_q_len) : launched;
   const double slots = (double)(kNumCUs * per_cu) * (ragged ? 0.8 : 1.0);
   const int64_t rows = (int64_t)total_q * (p->num_q_heads / p->num_kv_heads);
   const int64_t per_tile = (int64_t)lazy::kPrefillRowsPerBlock * prefill_row_blocks(p, max_q_len);

@@ -243,6 +243,17 @@ def test_prefill_split_count_stays_in_its_range(ops, d, batch, q_mean, q_max, kv
     assert n <= 256 << 20
 
 
+@pytest.mark.parametrize("hq,hkv,d,batch,q_max,kv", [(28, 4, 128, 4, 42, 45076), (8, 8, 128, 2, 275, 63959),
+                                                     (32, 8, 128, 4, 130, 2707), (40, 8, 128, 5, 72, 7461),
+                                                     (16, 1, 128, 4, 26, 138016), (32, 8, 64, 6, 150, 5000)])
+def test_prefill_splits_of_nearly_equal_batches_are_those_of_equal_ones(ops, hq, hkv, d, batch, q_max, kv):
+    """Query lengths from 3/4 of the longest on launch the same workgroups as equal ones, and get the same splits."""
+    cfg = ops.Config(hq, hkv, d, 5e5)
+    splits = [ops.prefill_workspace_size(cfg, batch, n, q_max, kv) // (n * hq * (2 * d + 4))
+              for n in (batch * q_max, batch * q_max - 1, (7 * batch * q_max) // 8, -(-3 * batch * q_max // 4))]
+    assert splits[0] > 1 and len(set(splits)) == 1, splits
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("batch,splits", [(20000, 2), (32767, 2), (32768, 1), (40000, 1), (65535, 1)])
 def test_prefill_split_count_is_held_to_the_grid(ops, d, batch, splits):

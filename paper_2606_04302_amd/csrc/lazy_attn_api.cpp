@@ -160,9 +160,13 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
 // Which workgroups of a ragged prefill stay together on an XCD.  One unit per KV head evens out the XCDs, one per request
 // and split reads its table once: the former from kUnitHeadsTiles tiles a split.  Four requests of 96-143K keys, two to
 // eight splits: 14.3 / 11.8 / 14.4 / 11.1 / 12.2 / 11.0 / 9.8 ms by request, 10.8 / 11.1 / 10.4 / 10.2 / 10.3 / 10.2 /
-// 10.1 by head (eight splits put a part of each request on every XCD); 16 requests of up to 27.6K keys in six splits (72
-// tiles) 809 -> 798 us; 11 of 9.9K in five (31 tiles) 335 -> 338; 16 of 4.7K in seven (10 tiles) 124.1 -> 126.3 us.
-constexpr int64_t kUnitHeadsTiles = 48;
+// 10.1 by head (eight splits put a part of each request on every XCD); 16 requests of up to 27.6K keys in five, eight and
+// nine splits (86, 54 and 48 tiles) 899 / 807 / 832 us by request, 822 / 794 / 811 by head.  Over 13148 ragged batches and
+// split counts by head is 0.3% slower under 2 tiles a split, 0.4% faster at 2 to 4, 0.9% at 4 to 8, 1.4% at 8 to 16, 1.5%
+// at 16 to 48 (a quarter of the batches gain more than 2%, one in thirty loses that) and 2.2% beyond; the line is not at
+// the crossing because short splits gain little and some lose (16 requests of 4.7K keys in seven, 10 tiles: 122.6 -> 123.5
+// us).
+constexpr int64_t kUnitHeadsTiles = 16;
 
 int prefill_units(int32_t batch, int32_t total_q, int32_t max_q_len, int32_t max_kv_len, int splits) {
   if (!prefill_ragged(batch, total_q, max_q_len)) return lazy::kUnitNone;

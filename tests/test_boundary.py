@@ -209,7 +209,7 @@ def test_workspace_size_matches_split_formula(ops):
 
 def test_prefill_xcd_map_choice(ops):
     """The interleaved XCD map applies to ragged batches (mean query length under 3/4 of the maximum) whose number of
-    units is a multiple of 8: batch x splits, or batch x splits x KV heads from 48 key tiles a split.  The prefill parity
+    units is a multiple of 8: batch x splits, or batch x splits x KV heads from 16 key tiles a split.  The prefill parity
     case varlen_g7_b8 is built to take it with the former."""
     w = W.varlen_rag(seed=30, batch=8, hq=28, hkv=4, d=128, pool_chunks=10, len_lo=40, len_hi=300, k_lo=2, k_hi=4,
                      q_lo=10, q_hi=90)
@@ -220,7 +220,7 @@ def test_prefill_xcd_map_choice(ops):
     splits = max(1, n // per_split)
     assert n == (0 if splits == 1 else splits * per_split)
     assert (w.batch * splits) % 8 == 0 and splits >= 2
-    assert w.max_kv_len // 64 < 48 * splits
+    assert w.max_kv_len // 64 < 16 * splits
     # several query tiles per KV head (256-row tiles at head_dim 128) and a ragged tail
     assert w.max_q_len * (w.num_q_heads // w.num_kv_heads) > 256
 

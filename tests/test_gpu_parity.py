@@ -1031,10 +1031,10 @@ def test_prefill_d64_three_waves(mode):
         run_and_check(w, f"prefill d64 three waves {mode} splits={splits}", {**OOO_MODES[mode], "num_splits": splits})
 
 
-# Ragged prefill batches place (request, split) units on XCDs, or (request, split, KV head) units from 48 tiles a split,
+# Ragged prefill batches place (request, split) units on XCDs, or (request, split, KV head) units from 16 tiles a split,
 # where their number is a multiple of 8 (by_request, by_head: whether it is), and run in grid order otherwise.  All of
 # these, with one and several row tiles.
-@pytest.mark.parametrize("tiles", [4, 47, 48])
+@pytest.mark.parametrize("tiles", [4, 15, 16])
 @pytest.mark.parametrize("hq,hkv,splits,batch,by_request,by_head",
                          [(16, 8, 1, 3, False, True), (28, 4, 2, 3, False, True), (28, 4, 3, 3, False, False),
                           (4, 1, 2, 3, False, False), (8, 2, 4, 3, False, True), (28, 4, 2, 4, True, True),
@@ -1046,9 +1046,9 @@ def test_ragged_prefill_unit_placement(hq, hkv, splits, batch, by_request, by_he
     reqs = [dict(chunks=[(k - n, 0), (n, k - n)], q_len=n, q_pos0=k - n) for k, n in zip(keys, lens)]
     w = W.custom(211, hq, hkv, d, 1e4, reqs)
     assert 4 * w.total_q < 3 * w.batch * w.max_q_len
-    heads = w.max_kv_len // 64 >= 48 * splits
+    heads = w.max_kv_len // 64 >= 16 * splits
     assert ((batch * splits * (hkv if heads else 1)) % 8 == 0) == (by_head if heads else by_request)
-    assert heads == (tiles == 48)
+    assert heads == (tiles == 16)
     run_and_check(w, f"ragged units {hq}/{hkv} d={d} q={q_max} splits={splits} batch={batch}", dict(num_splits=splits))
 
 

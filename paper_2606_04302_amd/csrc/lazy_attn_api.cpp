@@ -85,23 +85,27 @@ int64_t prefill_busy(const lazy_attn_params_t* p, int32_t batch, int32_t total_q
 // Until its first tile is done and at its end a workgroup spends about as long as on kPrologueTiles tiles; two or three
 // workgroups on a CU take 1.2 or 1.35 times as long each as one alone; a split batch is merged by a second launch.  A
 // count just past a full round runs the last one nearly empty.  Tiles: max_kv_len / 64, with 15% more for records that
-// end in a partial tile.  Ragged query lengths (mean below 3/4 of the maximum) usually come with ragged key lengths: the
-// average request is then taken as 0.8 of the longest, which sets the end; the units of different size fill 0.8 of the
-// slots, and the dispatcher evens out most of the last round (a quarter of it is counted as lost); 75% more tiles, since
-// splits too few are dearer there than splits too many.
+// end in a partial tile.
 //
-// The constants are a fit over split sweeps of 66 batches (128 and 256 rows, head_dim 64 and 128, busy 2 to 816, 4 to
-// 931 tiles): the chosen count is 4% off each batch's best on average.  One round for equal and three for ragged query
-// lengths, with at least four tiles a split, was 19% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
+// Ragged query lengths (mean below 3/4 of the maximum) usually come with ragged key lengths, which the call does not
+// tell.  A launch of no more than one round, empty workgroups among them, takes as long as its longest one: 1.4 per +
+// 4, per = max_kv_len / (64 splits).  A larger one takes 0.6 per + 7 for the average workgroup, times the rounds that
+// the busy ones make with 1.3 to a slot (shorter ones make room early), and 0.85 per + 4 for the longest at the end.
+// Just past one round the time jumps by up to half (three requests of up to 41 queries and 2.6K keys, 28 / 4 heads, 24
+// workgroups: ten splits 36 us, eleven 54).
+//
+// The constants are a fit over split sweeps of 5983 batches (128 and 256 rows, head_dim 64 and 128, all key modes,
+// contiguous and paged, 8 to 6775 tiles), checked on 4476 others: the chosen count is 3.7% off each batch's best of 1
+// to 64 on average, 1.9% if equal or nearly so and 5.8% if ragged.  One round for equal and three for ragged query
+// lengths, with at least four tiles a split, is 18% off: one request of 22 tiles, busy 8, five splits 23.5 us, twenty
 // 19.3; 8 requests of 95 tiles at head_dim 64, busy 256, one to four splits 178 / 126 / 107 / 123 us; ragged, busy 176,
-// 81 tiles, fifteen and five splits 153 / 127 us.  Longer batches than the fitted ones, eight of equal requests with
-// 1030 to 2340 tiles: the chosen count within 2% of the best of one to seventeen splits, on one 9% off (two splits 1.92
-// ms, seventeen 1.76).  Close estimates are followed too: nine requests of 2340 tiles at head_dim 64 get seventeen
-// splits on 1.7% less than for two, and take 3.01 ms instead of 3.44.  Four and six splits on four ragged batches of
-// busy 240 to 272 and 377 to 437 tiles, with units of one KV head (prefill_units): 790 / 798, 898 / 878, 800 / 779 and
-// 749 / 723 us.  Still missed: records much shorter than a tile, whose number the lengths do not tell (records of 6 to
-// 51 keys, busy 144: 166 us where eleven splits take 147; blocks of 32 keys, busy 176: 335 us where six take 313).
-constexpr double kPrologueTiles = 8, kRaggedPrologueTiles = 4, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
+// 81 tiles, fifteen and five splits 153 / 127 us.  4% of the batches are more than 5% faster that way.  Close estimates
+// are worth following: the least count within 3% of the least estimate would be 1.7% slower over the equal batches and
+// 0.3% over the ragged ones, and nine requests of 2340 tiles at head_dim 64 get seventeen splits on 1.7% less than for
+// two, and take 3.01 ms instead of 3.44.  Longer batches than the fitted ones, eight of equal requests with 1030 to
+// 2340 tiles: within 2% of the best of one to seventeen splits, on one 9% off.  Still missed: how the keys are spread
+// over a ragged batch's requests, and records much shorter than a tile.
+constexpr double kPrologueTiles = 8, kMergeTiles = 3, kMergeTilesPerSplit = 0.05;
 constexpr double kSharing[4] = {1, 1, 1.2, 1.35};
 constexpr int64_t kMaxSplits = 64;
 // A split batch's outputs pass through bf16 partials, an unsplit one's are rounded once (one request of 8 tiles, seven
@@ -122,7 +126,7 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   const bool ragged = prefill_ragged(batch, total_q, max_q_len);
   const double launched = (double)batch * prefill_q_tiles(p, max_q_len) * p->num_kv_heads;
   const double busy = ragged ? (double)prefill_busy(p, batch, total_q, max_q_len) : launched;
-  const double slots = (double)(kNumCUs * per_cu) * (ragged ? 0.8 : 1.0);
+  const double slots = (double)(kNumCUs * per_cu);
   const int64_t rows = (int64_t)total_q * (p->num_q_heads / p->num_kv_heads);
   const int64_t per_tile = (int64_t)lazy::kPrefillRowsPerBlock * prefill_row_blocks(p, max_q_len);
   const int64_t full = (int64_t)kNumCUs * (per_cu == 1 ? 1 : 2) * (ragged ? 3 : 1);
@@ -133,17 +137,16 @@ int prefill_splits(const lazy_attn_params_t* p, int32_t batch, int32_t total_q, 
   int64_t best = 1;
   double least = 0;
   for (int64_t s = 1; s <= most; ++s) {
-    const double groups = busy * (double)s, n = groups / slots;
+    const double groups = busy * (double)s, per = (double)tiles / (double)s;
     const double sharing = kSharing[(int)std::min((double)per_cu, std::ceil(groups / kNumCUs))];
     const double merge = s > 1 ? kMergeTiles + kMergeTilesPerSplit * (double)s : 0;
     double cost;
-    if (ragged) {
-      const double per = (1.75 * (double)tiles + 1) / (double)s;
-      cost = (0.25 * std::ceil(n) + 0.75 * std::max(1.0, n)) * (0.8 * per + kRaggedPrologueTiles) +
-             0.3 * (per + kRaggedPrologueTiles);
-    } else {
-      cost = std::ceil(n) * ((1.15 * (double)tiles + 1) / (double)s + kPrologueTiles);
-    }
+    if (!ragged)
+      cost = std::ceil(groups / slots) * ((1.15 * (double)tiles + 1) / (double)s + kPrologueTiles);
+    else if (launched * (double)s <= slots)
+      cost = 1.4 * per + 4;
+    else
+      cost = std::max(1.0, groups / (1.3 * slots)) * (0.6 * per + 7) + 0.85 * per + 4;
     cost = sharing * cost + merge;
     if (s == 1 || cost < least) {
       best = s;

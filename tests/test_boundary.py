@@ -254,6 +254,21 @@ def test_prefill_splits_of_nearly_equal_batches_are_those_of_equal_ones(ops, hq,
     assert splits[0] > 1 and len(set(splits)) == 1, splits
 
 
+@pytest.mark.parametrize("hq,hkv,batch,total_q,q_max,kv,tile_rows", [(16, 1, 29, 369, 21, 1035, 256),
+                                                                     (28, 4, 3, 83, 41, 2553, 256),
+                                                                     (16, 1, 4, 53, 23, 15503, 256),
+                                                                     (32, 8, 2, 56, 39, 3260, 128),
+                                                                     (28, 4, 2, 73, 56, 2320, 256)])
+def test_prefill_splits_of_small_ragged_batches_fill_one_round(ops, hq, hkv, batch, total_q, q_max, kv, tile_rows):
+    """Small ragged batches get the splits whose launch fills one round (one workgroup of 256 rows a CU, two of 128):
+    counts just past it take up to 1.5 times as long."""
+    assert 4 * total_q < 3 * batch * q_max
+    splits = ops.prefill_workspace_size(ops.Config(hq, hkv, 128, 5e5), batch, total_q, q_max, kv) // (total_q * hq * 260)
+    launched = batch * -(-q_max * (hq // hkv) // tile_rows) * hkv
+    round_ = 256 * (256 // tile_rows)
+    assert round_ - launched < launched * splits <= round_
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("batch,splits", [(20000, 2), (32767, 2), (32768, 1), (40000, 1), (65535, 1)])
 def test_prefill_split_count_is_held_to_the_grid(ops, d, batch, splits):

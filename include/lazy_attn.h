@@ -327,10 +327,13 @@ LAZY_API int lazy_shared_decode_plan(const lazy_attn_params_t* params, const laz
  * or the last-level cache, instead of each from memory.  The decode entry points already walk tables of up to 256
  * records in storage order by themselves (batches of several requests with at least 1536 keys per split, whatever
  * the cache hint): by v_offset, in units of 128 KiB with table order kept inside a unit, if some record of at least 128
- * keys is followed by one of an earlier unit.  Tables of shorter records alone (the blocks of a paged store) and longer
- * tables are walked as given.  A table given in storage order spares the sort (about 2 us with 129 records) and brings
- * the effect to those.  The chunk-major shared decode's planner wants tables in position order instead (it chains the
- * blocks a request reads back to back).  Returns LAZY_EINVAL for a bad chunk_start (not starting at 0, decreasing) or
+ * keys is followed by one of an earlier unit, and if the request seems to share its store with the next one of the
+ * batch: one of two records of that one's table, a third of it from either end, lies among its own with more than a
+ * sixteenth of them on either side (the order of a request's sums, not more, may thus depend on that table).  Tables of
+ * shorter records alone (the blocks of a paged store), contexts that a request has for itself and longer tables are
+ * walked as given.  A table given in storage order spares the sort (about 2 us with 129 records) and brings the effect
+ * to those.  The chunk-major shared decode's planner wants tables in position order instead (it chains the blocks a
+ * request reads back to back).  Returns LAZY_EINVAL for a bad chunk_start (not starting at 0, decreasing) or
  * missing arrays.
  */
 LAZY_API int lazy_chunk_table_storage_order(const lazy_chunk_t* chunks, const int32_t* chunk_start, int32_t batch,

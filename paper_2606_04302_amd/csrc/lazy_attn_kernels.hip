@@ -355,31 +355,41 @@ struct DecodeIter : TileIter<TK> {
     if (SORT && sorted) r = (uint32_t)__builtin_amdgcn_readlane((int)perm, r & 63) >> (8 * (r >> 6)) & 255;
     return load_rec(recs + r);
   }
-  __device__ void init(const lazy_chunk_t* table, int c0, int c1, int split, int splits,
-                       const typename Base::First& first) {
-    sorted = false;
-    Base::init(table, c0, c1, split, splits, first);
-  }
-  // order: the n <= kSortMax table indexes, sorted: their records, both in LDS.  The split's first two records come from
-  // there (a scalar load would be one more round trip before the first tile), the later ones from the table.
-  __device__ void init_sorted(const lazy_chunk_t* table, int c0, int n, int split, int splits, const uint8_t* order,
-                              const lazy_chunk_t* sorted_recs) {
-    sorted = true;
+  // order, sorted_recs: where `sort`, the table indexes and the records of the n <= kSortMax records in the order of the
+  // walk, both in LDS.  The split's first two records then come from there (a scalar load would be one more round trip
+  // before the first tile), the later ones from the table.  One copy of locate serves both walks (with two the kernel is
+  // 1.7 KB longer, and four requests of 33K keys at head_dim 64 whose tables are in order take 55.9 us instead of 55.1).
+  __device__ void init(const lazy_chunk_t* table, int c0, int c1, int split, int splits, typename Base::First f,
+                       bool sort = false, const uint8_t* order = nullptr, const lazy_chunk_t* sorted_recs = nullptr) {
+    sorted = SORT && sort;
+    if (!SORT) {
+      Base::init(table, c0, c1, split, splits, f);
+      return;
+    }
     recs = as_const(table + c0);
     const int lane = threadIdx.x & 63;
-    typename Base::First f;
-    f.mine.len = sorted_recs[lane].len;
-    perm = order[lane];
+    if (sorted) {
+      f.mine.len = sorted_recs[lane].len;
+      perm = order[lane];
 #pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      f.len[u] = sorted_recs[lane + 64 * (u + 1)].len;
-      perm |= (uint32_t)order[lane + 64 * (u + 1)] << (8 * (u + 1));
+      for (int u = 0; u < 3; ++u) {
+        f.len[u] = sorted_recs[lane + 64 * (u + 1)].len;
+        perm |= (uint32_t)order[lane + 64 * (u + 1)] << (8 * (u + 1));
+      }
     }
-    if (!Base::locate(table, 0, n, split, splits, f)) return;
-    // Lane 0 / 1 hold records i / i + 1 (the last one if there is none).
-    const lazy_chunk_t two = sorted_recs[min(i + (lane & 1), n - 1)];
-    cur = Base::lane_rec(two, 0);
-    if (i + 1 < end) nxt = Base::lane_rec(two, 1);
+    if (!Base::locate(table + c0, 0, c1 - c0, split, splits, f)) return;
+    if (sorted) {
+      // Lane 0 / 1 hold records i / i + 1 (the last one if there is none).
+      const lazy_chunk_t two = sorted_recs[min(i + (lane & 1), end - 1)];
+      cur = Base::lane_rec(two, 0);
+      if (i + 1 < end) nxt = Base::lane_rec(two, 1);
+    } else if (i < 64) {
+      cur = Base::lane_rec(f.mine, i);
+      if (i + 1 < end) nxt = i + 1 < 64 ? Base::lane_rec(f.mine, i + 1) : load_rec(recs + i + 1);
+    } else {
+      cur = load_rec(recs + i);
+      if (i + 1 < end) nxt = load_rec(recs + i + 1);
+    }
   }
   __device__ void step() {
     --left;
@@ -420,24 +430,36 @@ struct RecordSort {
   lazy_chunk_t recs[kSortMax] __attribute__((aligned(16)));
   uint32_t key[kSortMax] __attribute__((aligned(16)));
   uint8_t order[kSortMax];
-  uint32_t unordered[kThreads / 64];  // per wave: one of its records lies after its successor in the table
+  uint32_t seen[kThreads / 64];  // per wave: its records not after sample 0 and 1, ten bits each; kUnordered where one
+                                 // of its records lies after its successor in the table
+  static constexpr uint32_t kUnordered = 1u << 20;
   __device__ static uint32_t unit_of(u32x2 v_offset) { return (v_offset[0] >> 16 | v_offset[1] << 16) & 0xffffff; }
   // A record as two 16-byte words (a lazy_chunk_t variable would be indexed memory to the compiler, in LDS or scratch):
   // lo = k_offset, v_offset; hi = len, pos_offset, k_stride, v_stride.  next: v_offset of the record after it (of the
-  // last record: its own).
-  __device__ void publish(u32x4 lo, uint32_t len, u32x2 next, int t, int n) {
+  // last record: its own).  sample: V offsets of two records of another request.
+  __device__ void publish(u32x4 lo, uint32_t len, u32x2 next, const int64_t (&sample)[2], int t, int n) {
     const uint32_t unit = unit_of(u32x2{lo[2], lo[3]});
     key[t] = t < n ? unit << 8 | (uint32_t)t : 0xffffffffu;
-    const bool any = __any(t < n && (int)len >= kSortMinKeys && unit_of(next) < unit);
-    if ((t & 63) == 0) unordered[t >> 6] = any;
+    uint32_t f = __any(t < n && (int)len >= kSortMinKeys && unit_of(next) < unit) ? kUnordered : 0;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      f += (uint32_t)__builtin_popcountll(__ballot(t < n && unit <= ((uint32_t)(sample[s] >> 16) & 0xffffff))) << 10 * s;
+    if ((t & 63) == 0) seen[t >> 6] = f;
   }
-  // After publish's barrier: is there anything to sort?  A private context from an allocator that only grows is in
-  // order already, and table order is then the sorted order.  Only neighbours are compared, and only where the first of
-  // the two is not short: long records in disorder with short ones between them stay as they are.  So do short records
-  // alone: the blocks of a paged store lie in no order that requests share, and every record taken from the order costs
-  // a wave a little (seven requests of up to 460 blocks of 64 keys, head_dim 64: 64.5 us in table order, 68.8 sorted).
-  __device__ bool needed() const {
-    return uniform((int)(unordered[0] | unordered[1] | unordered[2] | unordered[3])) != 0;
+  // After publish's barrier: is there anything to sort?  A context from an allocator that only grows is in order already,
+  // and table order is then the sorted order.  Only neighbours are compared, and only where the first of the two is not
+  // short: long records in disorder with short ones between them stay as they are.  So do short records alone: the
+  // blocks of a paged store lie in no order that requests share, and every record taken from the order costs a wave a
+  // little (seven requests of up to 460 blocks of 64 keys, head_dim 64: 64.5 us in table order, 68.8 sorted).
+  // Nor is a context sorted that its request has for itself, which only costs (four private contexts of 128 shuffled
+  // records, 33K keys: 99.5 us in table order, 103.6 sorted, 100.2 with this test): the samples are records of the
+  // next request, a third of its table from either end, and where neither lies among this request's, with a sixteenth
+  // of them before it and as many after it, the two share no pool.  (A sixteenth, since the tokens a request generates
+  // lie apart from its context, after those of others.)
+  __device__ bool needed(int n) const {
+    const uint32_t f = (uint32_t)uniform((int)(seen[0] + seen[1] + seen[2] + seen[3]));
+    const int few = (n + 8) >> 4, below0 = f & 1023, below1 = f >> 10 & 1023;
+    return f >= kUnordered && ((below0 > few && n - below0 > few) || (below1 > few && n - below1 > few));
   }
   __device__ void place(u32x4 lo, u32x4 hi, int t, int n) {
     int rank = t;  // entries past n keep their place (the walk never reaches them)
@@ -1418,7 +1440,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int col = lane & 15, kq = lane >> 4;
   const int qpos = as_const(a.q_pos0)[r];
   const int c0 = as_const(a.chunk_start)[r], c1 = as_const(a.chunk_start)[r + 1];
+  const int rn = r + 1 < (int)gridDim.z ? r + 1 : 0;
+  const int n0 = SORT ? as_const(a.chunk_start)[rn] : 0, n1 = SORT ? as_const(a.chunk_start)[rn + 1] : 0;
   asm volatile("" ::"s"(qpos), "s"(c0), "s"(c1));  // one round trip for the three (the compiler would sink qpos)
+  if (SORT) asm volatile("" ::"s"(n0), "s"(n1));   // and for the next request's bounds
 
   const bool hvalid = col < hcount;
   const int head = g * G + kDecodeHeadsPerGroup * hg + (hvalid ? col : 0);
@@ -1429,6 +1454,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   static_assert(kSortMax == kThreads, "one record per thread");
   const TileIter<kDecWaveKeys>::First first = TileIter<kDecWaveKeys>::first_block(a.chunks, c0, c1);
   const bool sortable = SORT && c1 > c0 && c1 - c0 <= kSortMax;
+  int64_t sample[2] = {};  // V offsets of two records of the next request (the last one's: the first request)
   u32x4 rlo = {}, rhi = {};  // this thread's record (past the end: the last one, ignored below) and the next V offset
   u32x2 rnext = {};
   if (sortable) {
@@ -1436,6 +1462,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     rlo = rec[0];
     rhi = rec[1];
     rnext = *reinterpret_cast<const u32x2*>(&a.chunks[min(c0 + tid + 1, c1 - 1)].v_offset);
+    // (of an empty table: our first record)
+    sample[0] = as_const(a.chunks)[n1 > n0 ? n0 + (n1 - n0) / 3 : c0].v_offset;
+    sample[1] = as_const(a.chunks)[n1 > n0 ? n1 - 1 - (n1 - n0) / 3 : c0].v_offset;
   }
   u32x4 qraw[SP][2];
   {
@@ -1447,17 +1476,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // The sort's LDS lies in the V slices, which the tile loop first writes after the last barrier below.
   static_assert(sizeof(RecordSort) <= sizeof(sm.v), "the record order is formed in the V slices");
   RecordSort& rs = *reinterpret_cast<RecordSort*>(&sm.v[0][0]);
-  if (sortable) rs.publish(rlo, rhi[0], rnext, tid, c1 - c0);
+  if (sortable) {
+    asm volatile("" : "+s"(sample[0]), "+s"(sample[1]));  // the samples arrive here and not before the Q loads
+    rs.publish(rlo, rhi[0], rnext, sample, tid, c1 - c0);
+  }
   __syncthreads();
   // This wave's tiles: every fourth tile of the split, starting at tile `wave`.
   DecodeIter<kDecWaveKeys, SORT> it;
-  if (sortable && rs.needed()) {
+  bool sorted = false;
+  if (sortable && rs.needed(c1 - c0)) {
+    sorted = true;
     rs.place(rlo, rhi, tid, c1 - c0);
     __syncthreads();
-    it.init_sorted(a.chunks, c0, c1 - c0, split, a.splits, rs.order, rs.recs);
-  } else {
-    it.init(a.chunks, c0, c1, split, a.splits, first);
   }
+  it.init(a.chunks, c0, c1, split, a.splits, first, sorted, rs.order, rs.recs);
   it.skip(wave);
   bool have = it.seek_strided(a.causal, qpos, 4);
   DecTile<D> cur, nxt;

@@ -942,6 +942,63 @@ def test_decode_sorts_records_by_storage(n, length, hq, d, splits, mode):
             assert torch.equal(out.view(torch.int16), out_m.view(torch.int16))
 
 
+def _walk_sorted(tables):
+    """Which requests' records the decode takes in storage order (batches with at least 1536 keys per split): tables of
+    up to 256 records, one of 128 keys or more before its predecessor's unit, with one of two records of the next
+    request's table, a third of it from either end, among theirs: more than a sixteenth of them on either side of it."""
+    units = [t["v_offset"] >> 16 for t in tables]
+    res = []
+    for r, (t, u) in enumerate(zip(tables, units)):
+        n, nxt = len(t), units[(r + 1) % len(tables)]
+        few = (n + 8) // 16
+        below = [(u <= x).sum() for x in ((nxt[len(nxt) // 3], nxt[-1 - len(nxt) // 3]) if len(nxt) else u[:1])]
+        res.append(0 < n <= 256 and bool(((t["len"][:-1] >= 128) & (u[1:] < u[:-1])).any())
+                   and any(b > few and n - b > few for b in below))
+    return res
+
+
+# A context that its request has for itself is walked in table order: pools of their own, also behind a record that all
+# requests share and with tokens of their own stored behind all pools.  Two requests that share a pool before two that
+# do not; pools that alternate in the store; a next request without records.  Both hints.
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("n", [3, 8, 24, 150])
+@pytest.mark.parametrize("pools,expect", [("private", [False] * 4), ("prefix", [False] * 4), ("tails", [False] * 4),
+                                          ("halves", [True, False, False, False]), ("alternate", [True] * 4),
+                                          ("empty", None)])
+def test_decode_walks_private_contexts_in_table_order(pools, expect, n, splits):
+    rng = np.random.default_rng(n)
+    length = max(128, -(-1536 * splits // n))
+    store = W._Store(2, 128)
+    prefix = store.add(length)
+    own = [[store.add(length) for _ in range(n)] for _ in range(4)]
+    if pools == "alternate":
+        own = [sum(own, [])[r::4] for r in range(4)]
+    elif pools == "halves":
+        own[1] = own[0]
+    elif pools == "empty":
+        own[1] = []
+    own = [[o[i] for i in rng.permutation(len(o))] for o in own]
+    if pools == "prefix":
+        own = [[prefix] + o for o in own]
+    elif pools == "tails":
+        own = [o + [store.add(length)] for o in own]
+    uses = [[(c, length, k * length) for k, c in enumerate(o)] for o in own]
+    w = W._finish("private", "decode", 8, 2, 128, 1e4, store, uses, [1] * 4, [len(o) * length for o in own], rng)
+    assert w.max_kv_len // splits >= 1536
+    tables = [w.chunks[w.chunk_start[r]:w.chunk_start[r + 1]] for r in range(4)]
+    in_order = _walk_sorted(tables)
+    if n >= 24 and expect:
+        assert in_order == expect
+    walked = [t[np.argsort(t["v_offset"] >> 16, kind="stable")] if s else t for t, s in zip(tables, in_order)]
+    some = [r for r in range(4) if len(tables[r])]  # (a table without records is compared with the oracle alone)
+    walked = [t if len(t) else walked[0] for t in walked]
+    for hint in (ops.CACHE_DEFAULT, ops.CACHE_STREAM):
+        ckw = dict(num_splits=splits, cache_hint=hint)
+        dw, out, lse = run_and_check(w, f"decode {pools} n={n} splits={splits}", ckw)
+        o, l = _one_by_one(dw, ops.config_of(w, **ckw), walked)
+        assert torch.equal(out[some].view(torch.int16), o[some].view(torch.int16)) and torch.equal(lse[some], l[some])
+
+
 # The hint changes how K and V are read and not the order of a walk: tables that are sorted with the one are sorted with
 # the other (one request in storage order, one reversed, one shuffled).
 @pytest.mark.parametrize("splits", [1, 2])

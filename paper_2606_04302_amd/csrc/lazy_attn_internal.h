@@ -41,7 +41,7 @@ struct AttnArgs {
   int32_t alibi;              // 1: no rotation, ALiBi bias (LAZY_ALIBI); inv_freq then holds optional slopes
   int32_t q_prerot;           // 1: q arrives rotated at its own positions (rotations use -pos_offset / none)
   int32_t stream_kv;          // decode: 1 reads K / V with non-temporal loads (LAZY_CACHE_STREAM)
-  int32_t sort_records;       // decode: 1 walks each request's records in the order their values are stored
+  int32_t sort_records;       // decode: 1 may walk a request's records in the order their values are stored
   double rope_log2_base;      // log2(rope_base), computed on the host (unused with inv_freq)
   float scale_log2;           // softmax scale * log2(e)
 };

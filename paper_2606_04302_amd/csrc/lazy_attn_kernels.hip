@@ -341,7 +341,7 @@ struct TileIter {
 };
 
 // The decode's walk: the tiles w, w + 4, ... of a split for wave w.  SORT: the records of a request that has at most
-// kSortMax of them are taken in the order in which their values are stored (sort_records below); a longer table is
+// kSortMax of them are taken in the order in which their values are stored (RecordSort below); a longer table is
 // walked as it is.
 constexpr int kSortMax = 256;  // 64 lanes x 4 indexes of one byte
 constexpr int kSortMinKeys = 128;

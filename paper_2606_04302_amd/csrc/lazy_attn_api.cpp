@@ -200,9 +200,10 @@ int decode_splits(const lazy_attn_params_t* p, int32_t batch, int32_t max_kv_len
 // -> 608.  Sorting takes a workgroup 1-2 us and finding that there is nothing to sort, or that the request has its
 // chunks for itself, 0.3-0.9 us (four private contexts of 33K keys in order 102.2 -> 103.0 us, shuffled 99.5 -> 100.2,
 // with the stream hint 92.4 -> 92.7 and 90.8 -> 91.1; at head_dim 64 54.8 -> 55.2 and 55.6 -> 56.0; 64 of 4K 185.9 ->
-// 186.6), so it is left out where that shows: one request, or under 1536 keys per split (10K keys in 16 splits: 20.8 ->
-// 21.3 us; 52 requests of 6.4K keys in 5 splits, in order: 36.8 -> 38.1 us; two requests of 2.6K keys in 13 splits: 16.9
-// -> 17.3 us).  The cache hint has no say: it must not change a result.
+// 186.6; tables of 560 and 620 blocks of 32 keys 147.5 -> 148.6 and 127.6 -> 129.2), so it is left out where that shows:
+// one request, or under 1536 keys per split (10K keys in 16 splits: 20.8 -> 21.3 us; 52 requests of 6.4K keys in 5 splits,
+// in order: 36.8 -> 38.1 us; two requests of 2.6K keys in 13 splits: 16.9 -> 17.3 us).  The cache hint has no say: it must
+// not change a result.
 bool decode_sorted(int32_t batch, int splits, int32_t max_kv_len) {
   return batch > 1 && max_kv_len / splits >= 1536;
 }
